@@ -299,6 +299,17 @@ int dsattn_quantize_mxfp8(const void* src, void* codes, void* scales, long long 
  * x - shift must stay finite.
  */
 int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStream_t stream);
+
+/*
+ * dsattn_key_mean over more workgroups per head, with the same bits: workspace is a
+ * caller-owned, 16-byte aligned device buffer of at least
+ * dsattn_key_mean_workspace_bytes(BH, N, d) bytes that overlaps neither k nor mean_out; its
+ * contents are overwritten.  With a null workspace, or where that size is 0 (few keys, or d
+ * outside [32, 256]), the call is dsattn_key_mean.
+ */
+size_t dsattn_key_mean_workspace_bytes(int BH, int N, int d);
+int dsattn_key_mean_ws(const void* k, float* mean_out, int BH, int N, int d, void* workspace,
+                       size_t workspace_bytes, hipStream_t stream);
 int dsattn_quantize_mxfp8_shift(const void* src, const float* shift, void* codes, void* scales,
                                 long long rows, int row_len, long long group_rows,
                                 hipStream_t stream);

@@ -123,6 +123,11 @@ def lib():
         L.dsattn_key_mean.argtypes = [ctypes.c_void_p, ctypes.c_void_p] + [ctypes.c_int] * 3 + [
             ctypes.c_void_p]
         L.dsattn_key_mean.restype = ctypes.c_int
+        L.dsattn_key_mean_workspace_bytes.argtypes = [ctypes.c_int] * 3
+        L.dsattn_key_mean_workspace_bytes.restype = ctypes.c_size_t
+        L.dsattn_key_mean_ws.argtypes = [ctypes.c_void_p, ctypes.c_void_p] + [ctypes.c_int] * 3 + [
+            ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+        L.dsattn_key_mean_ws.restype = ctypes.c_int
         L.dsattn_last_error.argtypes = []
         L.dsattn_last_error.restype = ctypes.c_char_p
         L.dsattn_version.argtypes = []
@@ -180,6 +185,21 @@ def _stream(stream):
 
     s = torch.cuda.current_stream() if stream is None else stream
     return s.cuda_stream
+
+
+def _workspace(nbytes, device, stream):
+    """Scratch of one call, from the pool of the stream that the call runs on: once this
+    reference is gone, only later work of that stream can get the memory."""
+    import torch
+
+    if nbytes == 0:
+        return None
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def _out(q, o):
@@ -391,7 +411,10 @@ def dsattn_key_mean(k, out=None, stream=None):
         raise ValueError("k must be a contiguous bf16 GPU tensor [B, H, N, d]")
     B, H, N, d = (int(x) for x in k.shape)
     out = torch.empty((B, H, d), dtype=torch.float32, device=k.device) if out is None else out
-    rc = lib().dsattn_key_mean(k.data_ptr(), out.data_ptr(), B * H, N, d, _stream(stream))
+    need = lib().dsattn_key_mean_workspace_bytes(B * H, N, d)
+    ws = _workspace(need, k.device, stream)
+    rc = lib().dsattn_key_mean_ws(k.data_ptr(), out.data_ptr(), B * H, N, d,
+                                  None if ws is None else ws.data_ptr(), need, _stream(stream))
     _check(rc, "dsattn_key_mean")
     return out
 

@@ -668,7 +668,10 @@ int dsattn_quantize_mxfp8_shift(const void* src, const float* shift, void* codes
   return quantize(src, shift, codes, scales, rows, row_len, group_rows, stream);
 }
 
-int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStream_t stream) {
+namespace {
+
+int key_mean(const void* k, float* mean_out, int BH, int N, int d, void* workspace,
+             size_t workspace_size, hipStream_t stream) {
   if (BH < 0 || N < 0) return fail(DSATTN_EINVAL, "BH and N must be >= 0");
   if (BH > 65535) return fail(DSATTN_EINVAL, "BH must be <= 65535 (got %d)", BH);
   if (d < 8 || d > 1024 || (d & (d - 1)) != 0)
@@ -684,10 +687,40 @@ int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStr
     return fail(DSATTN_EINVAL, "k and mean_out must be device pointers");
   if (!aligned(k, 16) || !aligned(mean_out, 4))
     return fail(DSATTN_EINVAL, "k must be 16-byte and mean_out 4-byte aligned");
-  const hipError_t e = dsattn::launch_key_mean(k, mean_out, BH, N, d, stream);
+  float* split = nullptr;
+  const size_t need = workspace == nullptr ? 0 : dsattn::key_mean_split_bytes(BH, N, d);
+  if (need > 0) {
+    if (workspace_size < need)
+      return fail(DSATTN_EINVAL, "workspace too small: %zu bytes given, %zu needed",
+                  workspace_size, need);
+    if (!is_device_pointer(workspace) || !aligned(workspace, 16))
+      return fail(DSATTN_EINVAL, "workspace must be a 16-byte aligned device pointer");
+    const Span ws = span("workspace", workspace, need);
+    if (overlap(ws, span("k", k, (size_t)BH * (size_t)N * (size_t)d * 2)) ||
+        overlap(ws, span("mean_out", mean_out, (size_t)BH * (size_t)d * 4)))
+      return fail(DSATTN_EINVAL, "workspace must not overlap k or mean_out");
+    split = static_cast<float*>(workspace);
+  }
+  const hipError_t e = dsattn::launch_key_mean(k, mean_out, BH, N, d, split, stream);
   if (e != hipSuccess) return fail(DSATTN_ELAUNCH, "key mean launch failed: %s", hipGetErrorString(e));
   g_last_error.clear();
   return DSATTN_OK;
+}
+
+}  // namespace
+
+int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStream_t stream) {
+  return key_mean(k, mean_out, BH, N, d, nullptr, 0, stream);
+}
+
+size_t dsattn_key_mean_workspace_bytes(int BH, int N, int d) {
+  if (BH <= 0 || BH > 65535 || N <= 0 || d < 8 || d > 1024 || (d & (d - 1)) != 0) return 0;
+  return dsattn::key_mean_split_bytes(BH, N, d);
+}
+
+int dsattn_key_mean_ws(const void* k, float* mean_out, int BH, int N, int d, void* workspace,
+                       size_t workspace_size, hipStream_t stream) {
+  return key_mean(k, mean_out, BH, N, d, workspace, workspace_size, stream);
 }
 
 const char* dsattn_last_error(void) { return g_last_error.c_str(); }

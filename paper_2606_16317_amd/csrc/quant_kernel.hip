@@ -6,9 +6,11 @@
 // Every run of 32 consecutive values of a row is one block: it shares the power-of-two
 // scale 2^E with E = floor(log2(max |x|)) - 8, stored as the E8M0 code E + 127 (0 for an
 // all-zero block), and each value becomes the FP8 E4M3 number nearest to x / 2^E -- ties
-// to the even code, magnitudes above 448 saturating to 448.  One thread handles one
-// block: four 16-byte loads, two 16-byte stores and one scale byte, so consecutive lanes
-// touch consecutive memory; the kernel is pure HBM streaming.
+// to the even code, magnitudes above 448 saturating to 448.
+//
+// Four lanes share a block, eight values (one 16-byte load, one 8-byte store) each, so
+// every load and store of a wave covers consecutive bytes; a thread keeps kChunks loads
+// in flight.  The codes come from the hardware's pair conversion.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -20,138 +22,188 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
-// E4M3 code of a finite float, rounded to nearest with ties to the even code, saturating
-// at 448 (0x7e); -0 and values that round to zero give +0.
-__device__ __forceinline__ uint32_t e4m3_code(float y) {
-  const uint32_t bits = __float_as_uint(y);
-  const uint32_t sign = bits >> 31;
-  const uint32_t a = bits & 0x7fffffffu;
-  uint32_t code;
-  if (a >= 0x43e00000u) {                 // |y| >= 448
-    code = 0x7eu;
-  } else if (a < 0x3c800000u) {           // |y| < 2^-6: subnormal step 2^-9
-    code = (uint32_t)__builtin_rintf(__uint_as_float(a) * 512.0f);   // 0..8; 8 = 2^-6
-  } else {
-    const uint32_t e = (a >> 23) - 127u + 7u;        // biased E4M3 exponent, 1..15
-    const uint32_t m = a & 0x7fffffu;
-    uint32_t keep = m >> 20;
-    const uint32_t rem = m & 0xfffffu;
-    keep += (rem > 0x80000u || (rem == 0x80000u && (keep & 1u))) ? 1u : 0u;
-    code = (e << 3) + keep;                          // a mantissa carry bumps the exponent
-    if (code > 0x7eu) code = 0x7eu;
-  }
-  return code == 0 ? 0u : (code | (sign << 7));
+constexpr int kThreads = 256;
+constexpr int kChunks = 4;               // 8-value chunks per thread
+constexpr int kChunkValues = 8;
+
+// E4M3 codes of four finite floats (byte i from y[i]), rounded to nearest with ties to
+// the even code, saturating at 448 (0x7e).  The conversion keeps the sign of values that
+// round to zero; the byte arithmetic after it turns 0x80 into +0 (bit 7 of `nz` is set
+// where a byte's low seven bits are not all zero).
+__device__ __forceinline__ uint32_t e4m3_codes(const float* y) {
+  float c[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c[i] = __builtin_amdgcn_fmed3f(y[i], -448.0f, 448.0f);
+  int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
+  const uint32_t codes = (uint32_t)w;
+  const uint32_t low = codes & 0x7f7f7f7fu;
+  const uint32_t nz = low + 0x7f7f7f7fu;
+  return low | (codes & nz & 0x80808080u);
+}
+
+// Maximum over the four lanes of an aligned quad.
+__device__ __forceinline__ uint32_t quad_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true));  // lane ^ 1
+  x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true));  // lane ^ 2
+  return x;
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// SHIFT: every value first has its column's entry of a float32 shift vector subtracted
-// (rounded to nearest float32); row i uses vector i / group_rows.
+// One 8-value chunk: the block's scale code (the same in its four lanes) and this lane's
+// eight codes.  `sh` holds the shift of the chunk's columns (SHIFT only): every value first
+// has it subtracted (rounded to nearest float32).
 template <bool SHIFT>
-__global__ __launch_bounds__(kThreads) void quantize_mxfp8_kernel(
-    const u32x4* __restrict__ src, u32x4* __restrict__ codes, uint8_t* __restrict__ scales,
-    long long n_blocks, const float* __restrict__ shift, int blocks_per_row,
-    long long group_rows) {
-  const long long blk = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (blk >= n_blocks) return;
-  u32x4 w[4];
+__device__ __forceinline__ void quantize_chunk(const u32x4& w, const float (&sh)[kChunkValues],
+                                               u32x2& out, uint32_t& scode) {
+  float x[kChunkValues];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = src[blk * 4 + i];      // 32 bf16 values
-  float x[32];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[8 * i + 2 * j] = bf16_lo(w[i][j]);
-      x[8 * i + 2 * j + 1] = bf16_hi(w[i][j]);
-    }
+  for (int j = 0; j < 4; ++j) {
+    x[2 * j] = bf16_lo(w[j]);
+    x[2 * j + 1] = bf16_hi(w[j]);
+  }
+  // Bit pattern of max |x|: magnitudes of finite floats order as integers.
+  uint32_t amax;
   if constexpr (SHIFT) {
-    const long long row = blk / blocks_per_row;
-    const int cb = (int)(blk - row * blocks_per_row);
-    const float4* sh = reinterpret_cast<const float4*>(
-        shift + (row / group_rows) * (long long)blocks_per_row * 32 + cb * 32);
+    float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float4 s4 = sh[i];
-      x[4 * i] -= s4.x;
-      x[4 * i + 1] -= s4.y;
-      x[4 * i + 2] -= s4.z;
-      x[4 * i + 3] -= s4.w;
+    for (int i = 0; i < kChunkValues; ++i) {
+      x[i] -= sh[i];
+      m = fmaxf(m, fabsf(x[i]));
     }
-  }
-  float amax = 0.f;
+    amax = __float_as_uint(m);
+  } else {
+    u16x2 m = __builtin_bit_cast(u16x2, w[0] & 0x7fff7fffu);
 #pragma unroll
-  for (int i = 0; i < 32; ++i) amax = fmaxf(amax, fabsf(x[i]));
-  uint32_t scode = 0;
-  float inv = 1.f;
-  if (amax > 0.f) {
-    int e2;
-    (void)frexpf(amax, &e2);                 // amax = f * 2^e2, f in [0.5, 1)
-    const int e = e2 - 1 - 8;                // floor(log2 amax) - 8
-    scode = (uint32_t)min(254, max(0, e + 127));
-    inv = __uint_as_float((254u - scode) << 23);           // 2^(127 - scode), exact
+    for (int j = 1; j < 4; ++j)
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
+    amax = (uint32_t)max(m[0], m[1]) << 16;
   }
-  u32x4 out[2];
+  amax = quad_max(amax);
+  // floor(log2 amax) - 8 + 127 is the biased exponent minus 8; zero and tiny blocks (and
+  // subnormal maxima, whose biased exponent is 0) clamp to code 0.
+  const int e = (int)(amax >> 23) - 8;
+  scode = (uint32_t)min(254, max(0, e));
+  const float inv = __uint_as_float((254u - scode) << 23);   // 2^(127 - scode), exact
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t packed = e4m3_code(x[4 * i] * inv) | (e4m3_code(x[4 * i + 1] * inv) << 8) |
-                            (e4m3_code(x[4 * i + 2] * inv) << 16) |
-                            (e4m3_code(x[4 * i + 3] * inv) << 24);
-    out[i >> 2][i & 3] = packed;
-  }
-  codes[blk * 2] = out[0];
-  codes[blk * 2 + 1] = out[1];
-  scales[blk] = (uint8_t)scode;
+  for (int i = 0; i < kChunkValues; ++i) x[i] *= inv;
+  out = u32x2{e4m3_codes(x), e4m3_codes(x + 4)};
 }
 
-// Mean over the N keys of every head.  Workgroup (g, h) takes column group g of head h:
+// blockIdx.y (in steps of gridDim.y) is the group of rows that shares a shift vector (one
+// group without SHIFT), blockIdx.x a run of kThreads * kChunks chunks of that group; thread
+// t takes chunks t, t + kThreads, ... of the run.  chunks_per_row is a multiple of 4, so
+// blocks never straddle groups and a quad of lanes is in range together.
+//
+// What bounds it: HBM, 3.03 bytes moved per value.  One thread per block with the codes
+// formed by integer arithmetic (about 20 operations per value, strided 16-byte loads) was
+// bound by the VALU instead: 720p K or Q
+// (40 x 75600 x 128, 1.17 GB) 232 us, now 204 (5.8 TB/s); with a shift 277, now 204.
+template <bool SHIFT>
+__global__ __launch_bounds__(kThreads) void quantize_mxfp8_kernel(
+    const u32x4* __restrict__ src, u32x2* __restrict__ codes, uint8_t* __restrict__ scales,
+    long long n_chunks, const float* __restrict__ shift, uint32_t chunks_per_row,
+    long long group_chunks) {
+  const long long first = (long long)blockIdx.x * (kThreads * kChunks) + threadIdx.x;
+  for (long long g = blockIdx.y; g * group_chunks < n_chunks; g += gridDim.y) {
+    const long long base = g * group_chunks;
+    const long long count = min(group_chunks, n_chunks - base);
+    u32x4 w[kChunks];
+#pragma unroll
+    for (int u = 0; u < kChunks; ++u)
+      w[u] = first + u * kThreads < count ? src[base + first + u * kThreads] : u32x4{0, 0, 0, 0};
+    float sh[kChunkValues];
+    uint32_t col = 0;
+    if constexpr (SHIFT) col = (uint32_t)(first % chunks_per_row);
+#pragma unroll
+    for (int u = 0; u < kChunks; ++u) {
+      if constexpr (SHIFT) {
+        // The column advances by kThreads per chunk: rows of 32, 64, ... 2048 values come
+        // back to the same one, so their shift is loaded once.
+        if (u == 0 || kThreads % chunks_per_row != 0) {
+          const float4* s4 = reinterpret_cast<const float4*>(
+              shift + (g * chunks_per_row + col) * kChunkValues);
+          const float4 a = s4[0], b = s4[1];
+          sh[0] = a.x; sh[1] = a.y; sh[2] = a.z; sh[3] = a.w;
+          sh[4] = b.x; sh[5] = b.y; sh[6] = b.z; sh[7] = b.w;
+          col = (col + kThreads) % chunks_per_row;
+        }
+      }
+      u32x2 out;
+      uint32_t scode;
+      quantize_chunk<SHIFT>(w[u], sh, out, scode);
+      const long long chunk = first + u * kThreads;
+      if (chunk < count) {
+        codes[base + chunk] = out;
+        if ((threadIdx.x & 3) == 0) scales[(base + chunk) >> 2] = (uint8_t)scode;
+      }
+    }
+  }
+}
+
+// Mean over the N keys of every head.  A workgroup takes one column group of a head:
 // kMeanCols columns (64 bytes of every row; all of a row when d is smaller).  Thread t
 // sums 16-byte chunk t % C of rows t / C, t / C + P, ... (C chunks per group, P =
-// kMeanThreads / C rows in flight per step, eight steps unrolled); then the P partial sums
-// of every column are added in row order from LDS.  The order is fixed, so repeated
-// calls agree bit for bit.
+// kMeanThreads / C rows in flight per step, kMeanUnroll steps' loads issued together); then
+// the P partial sums of every column are added in row order from LDS.  The order is fixed,
+// so repeated calls agree bit for bit.
+//
+// What bounds it: HBM at many heads, and at few heads the loads one workgroup can keep in
+// flight.  A head's column groups share 128-byte lines, so they go to the same XCD (L2), one
+// after the other in its dispatch order (720p K, 774 MB: 222 us, now 196).
 constexpr int kMeanThreads = 256;
 constexpr int kMeanCols = 32;
+constexpr int kMeanUnroll = 8;
+constexpr int kMeanPhases = kMeanThreads / (kMeanCols / 8);   // partial sums for d >= 32
+constexpr int kXcds = 8;       // accelerator dies; workgroups are dealt to them round-robin
 
 __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __restrict__ k,
                                                                 float* __restrict__ mean,
-                                                                int N, int d) {
+                                                                int bh, int N, int d) {
   __shared__ float part[kMeanThreads * 8];
   const int cols = d < kMeanCols ? d : kMeanCols;
+  const int groups = d / cols;
+  const int slot = (int)(blockIdx.x / kXcds);          // place in this XCD's order
+  const int head = (slot / groups) * kXcds + (int)(blockIdx.x % kXcds);
+  const int group = slot % groups;
+  if (head >= bh) return;
   const int cpg = cols >> 3;                 // 16-byte chunks per group and row
   const int cpr = d >> 3;                    // chunks per row
   const int par = kMeanThreads / cpg;        // rows per step
   const int t = threadIdx.x;
   const int c = t % cpg;
-  const int head = blockIdx.y;
-  const u32x4* base = k + (size_t)head * (size_t)N * cpr + (size_t)blockIdx.x * cpg + c;
+  const u32x4* base = k + (size_t)head * (size_t)N * cpr + (size_t)group * cpg + c;
   float acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  int r = t / cpg;
-  for (; r + 7 * par < N; r += 8 * par) {
-    u32x4 x[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = base[(size_t)(r + u * par) * cpr];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc[2 * j] += bf16_lo(x[u][j]);
-        acc[2 * j + 1] += bf16_hi(x[u][j]);
-      }
-  }
-  for (; r < N; r += par) {
-    const u32x4 x = base[(size_t)r * cpr];
+  auto add = [&](const u32x4& x) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       acc[2 * j] += bf16_lo(x[j]);
       acc[2 * j + 1] += bf16_hi(x[j]);
     }
+  };
+  int r = t / cpg;
+  for (; r + (kMeanUnroll - 1) * par < N; r += kMeanUnroll * par) {
+    u32x4 x[kMeanUnroll];
+#pragma unroll
+    for (int u = 0; u < kMeanUnroll; ++u) x[u] = base[(size_t)(r + u * par) * cpr];
+#pragma unroll
+    for (int u = 0; u < kMeanUnroll; ++u) add(x[u]);
   }
+  for (; r + 3 * par < N; r += 4 * par) {
+    u32x4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = base[(size_t)(r + u * par) * cpr];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(x[u]);
+  }
+  for (; r < N; r += par) add(base[(size_t)r * cpr]);
 #pragma unroll
   for (int i = 0; i < 8; ++i) part[t * 8 + i] = acc[i];
   __syncthreads();
@@ -159,9 +211,75 @@ __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __r
   for (int e = t; e < cols; e += kMeanThreads) {
     const int ch = e >> 3, i = e & 7;
     float sum = 0.f;
-    for (int rl = 0; rl < par; ++rl) sum += part[(rl * cpg + ch) * 8 + i];
-    mean[(size_t)head * d + (size_t)blockIdx.x * cols + e] = sum * inv_n;
+    for (int rl = 0; rl < par; rl += 32) {   // par is 64 to 256: 32 reads in flight
+      float x[32];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) x[u] = part[((rl + u) * cpg + ch) * 8 + i];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) sum += x[u];
+    }
+    mean[(size_t)head * d + (size_t)group * cols + e] = sum * inv_n;
   }
+}
+
+// The same sums with a head's rows spread over d / 4 workgroups of one wave, for which the
+// caller provides memory.  A lane takes four columns (8 bytes) of the rows of one phase p
+// (p, p + kMeanPhases, ...), a wave 256 / d phases over all columns, so that it reads whole
+// rows; the sums of a phase and their final order are those of key_mean_kernel, and so are
+// the bits.
+//
+// Why: a workgroup of key_mean_kernel reads at about 25 GB/s however many loads it has in
+// flight (line fills of its CU: each 64-byte piece brings in a whole line), and a head has
+// only four.  40 heads of 75600 keys: 196 us against 129 (6.0 TB/s); 5 heads of 32760:
+// 41 against 25.  At 2 x 8192 keys the second launch costs more than it saves (9 against
+// 13 us), so the split starts at kMeanSplitRows keys.
+constexpr int kMeanSplitUnroll = 16;
+constexpr int kMeanSplitRows = 16384;
+
+__global__ __launch_bounds__(64) void key_mean_phases_kernel(const u32x2* __restrict__ k,
+                                                             float4* __restrict__ part, int N,
+                                                             int d) {
+  const int lpr = d >> 2;                    // lanes per row; also workgroups per head
+  const int t = threadIdx.x;
+  const int c = t % lpr;
+  const int phase = (int)blockIdx.x * (64 / lpr) + t / lpr;
+  const size_t head = blockIdx.y;
+  const u32x2* base = k + head * (size_t)N * lpr + c;
+  float4 acc{0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const u32x2& x) {
+    acc.x += bf16_lo(x[0]);
+    acc.y += bf16_hi(x[0]);
+    acc.z += bf16_lo(x[1]);
+    acc.w += bf16_hi(x[1]);
+  };
+  int r = phase;
+  for (; r + (kMeanSplitUnroll - 1) * kMeanPhases < N; r += kMeanSplitUnroll * kMeanPhases) {
+    u32x2 x[kMeanSplitUnroll];
+#pragma unroll
+    for (int u = 0; u < kMeanSplitUnroll; ++u) x[u] = base[(size_t)(r + u * kMeanPhases) * lpr];
+#pragma unroll
+    for (int u = 0; u < kMeanSplitUnroll; ++u) add(x[u]);
+  }
+  for (; r < N; r += kMeanPhases) add(base[(size_t)r * lpr]);
+  part[(head * kMeanPhases + phase) * (size_t)lpr + c] = acc;
+}
+
+// mean[head][col] from the phase sums [head][kMeanPhases][d], added in phase order.
+__global__ __launch_bounds__(64) void key_mean_join_kernel(const float* __restrict__ part,
+                                                           float* __restrict__ mean, int N, int d,
+                                                           int n_cols) {
+  const int e = (int)(blockIdx.x * 64 + threadIdx.x);     // column of all heads' columns
+  if (e >= n_cols) return;
+  const size_t head = (size_t)(e / d);
+  const float* p = part + head * kMeanPhases * d + (e - head * d);
+  float x[kMeanPhases];
+#pragma unroll
+  for (int u = 0; u < kMeanPhases; ++u) x[u] = p[(size_t)u * d];
+  const float inv_n = 1.0f / (float)N;
+  float sum = 0.f;
+#pragma unroll
+  for (int u = 0; u < kMeanPhases; ++u) sum += x[u];
+  mean[e] = sum * inv_n;
 }
 
 }  // namespace
@@ -169,25 +287,48 @@ __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __r
 hipError_t launch_quantize_mxfp8(const void* src, void* codes, void* scales,
                                  long long n_blocks, const float* shift, int blocks_per_row,
                                  long long group_rows, hipStream_t stream) {
-  const long long grid = (n_blocks + kThreads - 1) / kThreads;
+  const long long n_chunks = n_blocks * 4;
+  const long long cpr = (long long)blocks_per_row * 4;
+  // Without a shift the whole array is one group; a group longer than the array is too.
+  const long long rows = n_blocks / blocks_per_row;
+  const bool one = shift == nullptr || group_rows >= rows;
+  const long long group_chunks = one ? n_chunks : group_rows * cpr;
+  const long long groups = (n_chunks + group_chunks - 1) / group_chunks;
+  const long long runs = (group_chunks + kThreads * kChunks - 1) / (kThreads * kChunks);
+  const dim3 grid((unsigned)runs, (unsigned)(groups < 65535 ? groups : 65535));
   if (shift == nullptr)
-    hipLaunchKernelGGL(quantize_mxfp8_kernel<false>, dim3((unsigned)grid), dim3(kThreads), 0,
-                       stream, static_cast<const u32x4*>(src), static_cast<u32x4*>(codes),
-                       static_cast<uint8_t*>(scales), n_blocks, shift, blocks_per_row,
-                       group_rows);
+    hipLaunchKernelGGL(quantize_mxfp8_kernel<false>, grid, dim3(kThreads), 0, stream,
+                       static_cast<const u32x4*>(src), static_cast<u32x2*>(codes),
+                       static_cast<uint8_t*>(scales), n_chunks, shift, (uint32_t)cpr,
+                       group_chunks);
   else
-    hipLaunchKernelGGL(quantize_mxfp8_kernel<true>, dim3((unsigned)grid), dim3(kThreads), 0,
-                       stream, static_cast<const u32x4*>(src), static_cast<u32x4*>(codes),
-                       static_cast<uint8_t*>(scales), n_blocks, shift, blocks_per_row,
-                       group_rows);
+    hipLaunchKernelGGL(quantize_mxfp8_kernel<true>, grid, dim3(kThreads), 0, stream,
+                       static_cast<const u32x4*>(src), static_cast<u32x2*>(codes),
+                       static_cast<uint8_t*>(scales), n_chunks, shift, (uint32_t)cpr,
+                       group_chunks);
   return hipGetLastError();
 }
 
-hipError_t launch_key_mean(const void* k, float* mean, int bh, int N, int d,
+size_t key_mean_split_bytes(int bh, int N, int d) {
+  if (bh <= 0 || N < kMeanSplitRows || d < kMeanCols || d > 256) return 0;
+  return (size_t)bh * kMeanPhases * (size_t)d * sizeof(float);
+}
+
+hipError_t launch_key_mean(const void* k, float* mean, int bh, int N, int d, float* split,
                            hipStream_t stream) {
+  if (split != nullptr) {
+    const int n_cols = bh * d;
+    hipLaunchKernelGGL(key_mean_phases_kernel, dim3((unsigned)(d / 4), (unsigned)bh), dim3(64), 0,
+                       stream, static_cast<const u32x2*>(k), reinterpret_cast<float4*>(split), N,
+                       d);
+    hipLaunchKernelGGL(key_mean_join_kernel, dim3((unsigned)((n_cols + 63) / 64)), dim3(64), 0,
+                       stream, split, mean, N, d, n_cols);
+    return hipGetLastError();
+  }
   const int groups = d < kMeanCols ? 1 : d / kMeanCols;
-  hipLaunchKernelGGL(key_mean_kernel, dim3((unsigned)groups, (unsigned)bh), dim3(kMeanThreads),
-                     0, stream, static_cast<const u32x4*>(k), mean, N, d);
+  const long long grid = (long long)((bh + kXcds - 1) / kXcds) * kXcds * groups;
+  hipLaunchKernelGGL(key_mean_kernel, dim3((unsigned)grid), dim3(kMeanThreads), 0, stream,
+                     static_cast<const u32x4*>(k), mean, bh, N, d);
   return hipGetLastError();
 }
 

@@ -15,9 +15,14 @@ hipError_t launch_quantize_mxfp8(const void* src, void* codes, void* scales,
                                  long long n_blocks, const float* shift, int blocks_per_row,
                                  long long group_rows, hipStream_t stream);
 
+// Bytes of device memory with which launch_key_mean spreads a head's rows over more
+// workgroups (0: the problem gains nothing from it).
+size_t key_mean_split_bytes(int bh, int N, int d);
+
 // mean[h][c] = (1/N) sum_n k[h][n][c] for bh heads of N rows of d bf16 values (d a power
-// of two in [8, 1024], k 16-byte aligned); deterministic.
-hipError_t launch_key_mean(const void* k, float* mean, int bh, int N, int d,
+// of two in [8, 1024], k 16-byte aligned); deterministic.  `split`: null, or 16-byte aligned
+// memory of key_mean_split_bytes() > 0 bytes; the result has the same bits either way.
+hipError_t launch_key_mean(const void* k, float* mean, int bh, int N, int d, float* split,
                            hipStream_t stream);
 
 }  // namespace dsattn

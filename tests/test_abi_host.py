@@ -333,6 +333,10 @@ def test_key_mean_and_shifted_quantize_host_checks():
     rc, err = _call_raw("dsattn_key_mean", p, p, 1, 4, 128, None)
     assert rc == -1 and "device pointers" in err
     assert _call_raw("dsattn_key_mean", None, None, 0, 4, 128, None) == (0, "")
+    rc, err = _call_raw("dsattn_key_mean_ws", p, p, 1, 4, 96, None, 0, None)
+    assert rc == -1 and "power of two" in err
+    rc, err = _call_raw("dsattn_key_mean_ws", p, p, 1, 4, 128, None, 0, None)
+    assert rc == -1 and "device pointers" in err
     rc, err = _call_raw("dsattn_quantize_mxfp8_shift", None, None, None, None, 4, 128, 4, None)
     assert rc == -1 and "shift must be non-null" in err
     rc, err = _call_raw("dsattn_quantize_mxfp8_shift", None, p, None, None, 4, 128, 0, None)

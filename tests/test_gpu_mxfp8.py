@@ -111,6 +111,26 @@ def test_quantize_empty_and_row_len_32():
     np.testing.assert_array_equal(codes, want_c)
 
 
+@pytest.mark.parametrize("rows,row_len", [(1, 32), (31, 32), (9, 96), (257, 128), (1025, 128),
+                                          (3, 2080)])
+def test_quantize_every_bf16_pattern_and_run_edges(rows, row_len):
+    """Row counts around one workgroup's run of 1024 eight-value chunks (8192 values), and
+    rows whose chunks do not divide it; the values run over every finite bf16 pattern, in
+    blocks whose other values lie within a few octaves and in blocks that mix all of them."""
+    announce(f"mxfp8 patterns rows={rows} row_len={row_len}")
+    pats = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    pats = pats[(pats & 0x7f80) != 0x7f80]                       # finite
+    near = np.concatenate([pats, np.random.default_rng(6).permutation(pats)])
+    reps = -(-rows * row_len // near.size)
+    bits = np.tile(near, reps)[:rows * row_len].reshape(1, 1, rows, row_len)
+    for part in (bits, bits[..., ::-1], np.roll(np.tile(near, reps), 40961)[:bits.size]
+                 .reshape(bits.shape)):
+        codes, scales = run(np.ascontiguousarray(part))
+        want_c, want_s = quantize_mxfp8(bf16_to_f64(np.ascontiguousarray(part)))
+        np.testing.assert_array_equal(scales, want_s)
+        np.testing.assert_array_equal(codes, want_c)
+
+
 # ---- attention with MX-FP8 Q and K --------------------------------------------------------
 
 SCALE = 1.0 / math.sqrt(128)
@@ -307,6 +327,50 @@ def test_shifted_quantize_bit_exact(N, seed):
     want_c, want_s = quantize_mxfp8(smooth_keys(kf, shift).astype(np.float64))
     np.testing.assert_array_equal(scales.cpu().numpy(), want_s)
     np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
+
+
+@pytest.mark.parametrize("H,N,d", [(2, 1, 96), (3, 37, 96), (2, 65, 2080), (2, 256, 32),
+                                   (2, 255, 128), (3, 513, 256)])
+def test_shifted_quantize_row_lengths(H, N, d):
+    """Rows whose chunks do and do not divide a workgroup's stride (the shift is then loaded
+    once or per chunk), groups that end inside a workgroup's run."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"shifted quantize H={H} N={N} row_len={d}")
+    bits = make_random_qkv(1, H, N, d, 50 + N, k_std=2.0)[1]
+    kf = bf16_to_f64(bits)
+    shift = np.random.default_rng(N).standard_normal((1, H, d)).astype(np.float32)
+    codes, scales = dsa.dsattn_quantize_mxfp8(to_device(bits),
+                                              shift=torch.from_numpy(shift).cuda())
+    want_c, want_s = quantize_mxfp8(smooth_keys(kf, shift).astype(np.float64))
+    np.testing.assert_array_equal(scales.cpu().numpy(), want_s)
+    np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
+
+
+@pytest.mark.parametrize("H,N,d", [(1, 16384, 128), (2, 16385, 32), (3, 17407, 256),
+                                   (2, 16384 + 1024 * 2 + 63, 64), (9, 20001, 128)])
+def test_key_mean_split_has_the_same_bits(H, N, d):
+    """From 16384 keys on the binding hands the call memory and a head's rows are spread over
+    more workgroups: the bits are those of the call without that memory."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"key mean split H={H} N={N} d={d}")
+    L = dsa.lib()
+    assert L.dsattn_key_mean_workspace_bytes(H, N, d) == H * 64 * d * 4
+    assert L.dsattn_key_mean_workspace_bytes(H, 16383, d) == 0
+    g = torch.Generator(device="cuda").manual_seed(N)
+    k = (torch.randn(1, H, N, d, device="cuda", generator=g) + 0.5).to(torch.bfloat16)
+    plain = torch.full((1, H, d), float("nan"), device="cuda")
+    assert L.dsattn_key_mean(k.data_ptr(), plain.data_ptr(), H, N, d,
+                             torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(plain, dsa.dsattn_key_mean(k))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    out = dsa.dsattn_key_mean(k, stream=side)
+    side.synchronize()
+    assert torch.equal(plain, out)
 
 
 def smoothed_codes(k):
