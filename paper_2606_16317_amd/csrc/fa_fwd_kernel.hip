@@ -95,8 +95,7 @@ constexpr int kMaxMaskTiles = 4096;
 struct MaskSmem {
   Smem t;
   alignas(4) uint16_t list[kMaxMaskTiles];   // (key tile << 4) | keep bit of each wave
-  alignas(4) uint16_t count[kThreads];       // kept tiles per thread, then their prefix
-  uint32_t total;                            // number of visited tiles
+  uint32_t count[kMaxMaskTiles / 64];        // visited tiles in each run of 64
 };
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -436,12 +435,9 @@ __device__ __forceinline__ void kept_tile(RowState& rs, f32x16 (&o)[4], const f3
                                           float m_hat, float c, f32x16 (&s_next)[2],
                                           const uint16_t* kt, const uint16_t* vt,
                                           const bf16x8 (&qf)[8], int r, int g, int lane,
-                                          float& rmax_next, bool contribute = true) {
-  // contribute == false (uniform): the tile runs the same instructions but adds nothing --
-  // exp2(S c - inf) = 0 for every element (S is finite or -inf), and the running max and
-  // sum stay as they are.
-  if (contribute) rescale_if_needed(rs, o, m_hat);
-  const float neg_m = contribute ? -rs.m_ref : -__builtin_inff();
+                                          float& rmax_next) {
+  rescale_if_needed(rs, o, m_hat);
+  const float neg_m = -rs.m_ref;
   float xs[32];
   bf16x8 pf[4];
   constexpr int RK = 3;   // operand ring: reads issued two MFMAs ahead
@@ -490,6 +486,72 @@ __device__ __forceinline__ void kept_tile(RowState& rs, f32x16 (&o)[4], const f3
 #pragma unroll
   for (int e = 0; e < 32; ++e) psum += xs[e];
   rs.l_half += psum;
+}
+
+// Kept tile j: softmax of S_j interleaved with the 16 MFMAs of S_{j+1} = K_{j+1} Q^T,
+// then O += P V_j.  MFMA operands are read from LDS two MFMAs ahead.
+// Visited tile j of a reused mask with 32-row units: as kept_tile when the wave's unit keeps
+// tile j (`contribute`, uniform); otherwise S_{j+1} only, the softmax slots running on
+// exp2(-inf) = 0 and the P V phase left out.  (Branching around the P V phase alone keeps
+// one copy of the Q K^T phase; with two whole tile bodies under the branch the kernel
+// spills 90 to 300 registers and takes three times as long.)
+__device__ __forceinline__ void unit_tile(RowState& rs, f32x16 (&o)[4], const f32x16 (&s_cur)[2],
+                                          float m_hat, float c, f32x16 (&s_next)[2],
+                                          const uint16_t* kt, const uint16_t* vt,
+                                          const bf16x8 (&qf)[8], int r, int g, int lane,
+                                          float& rmax_next, bool contribute) {
+  if (contribute) rescale_if_needed(rs, o, m_hat);
+  const float neg_m = contribute ? -rs.m_ref : -__builtin_inff();
+  float xs[32];
+  bf16x8 pf[4];
+  constexpr int RK = 3;   // operand ring, as in kept_tile
+  bf16x8 ka[RK], va[RK];
+#pragma unroll
+  for (int i = 0; i < RK - 1; ++i) ka[i] = k_operand(kt, i, r, g);
+  sched_fence();
+  __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (i + RK - 1 < 16)
+      ka[(i + RK - 1) % RK] = k_operand(kt, i + RK - 1, r, g);
+    else
+      va[i + RK - 1 - 16] = v_operand(vt, i + RK - 1 - 16, lane);
+    f32x16& acc = s_next[i & 1];
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i % RK], qf[i >> 1],
+                                                  i < 2 ? f32x16{} : acc, 0, 0, 0);
+    if (i < 8) {
+      softmax_elem_keep(s_cur, 2 * i, c, neg_m, xs, pf);
+      softmax_elem_keep(s_cur, 2 * i + 1, c, neg_m, xs, pf);
+    } else {
+      softmax_elem_keep(s_cur, 16 + (i - 8), c, neg_m, xs, pf);
+    }
+    sched_fence();
+  }
+  if (contribute) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i + RK - 1 < 16) va[(i + RK - 1) % RK] = v_operand(vt, i + RK - 1, lane);
+      o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i % RK], pf[i >> 2], o[i & 3], 0, 0, 0);
+      if (i < 8) {
+        softmax_elem_keep(s_cur, 24 + i, c, neg_m, xs, pf);
+      } else {
+        if (i == 8) rmax_next = s_next[0][0];
+        row_max_part(s_next, i - 8, rmax_next);
+      }
+      sched_fence();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    float psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) psum += xs[e];
+    rs.l_half += psum;
+  } else {
+    __builtin_amdgcn_s_setprio(0);
+    rmax_next = s_next[0][0];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) row_max_part(s_next, k, rmax_next);
+  }
+  rmax_next = row_max_join(rmax_next);
 }
 
 // Kept tile j on the MX-FP8 path: as kept_tile, with S_{j+1} from four scaled fp8 MFMAs
@@ -1514,16 +1576,24 @@ __device__ __forceinline__ void mask_tile_step(int j, int n_keep, const f32x16 (
   const int tn2 = (int)(e2 >> 4);
   const uint32_t e3_raw = j + 3 < n_keep ? (uint32_t)sm.list[j + 3]
                                          : (uint32_t)cx.n_kt << 4;
-  bool keep_own = true;
-  if constexpr (UNIT != kTQ) keep_own = ((e0 >> cx.w) & 1u) != 0;
   load_tile_lds(sm.t.v[nb], cx.vrs, cx.voff, tn * kTK, cx.w);
   load_tile_lds(sm.t.k[j & 1], cx.krs, cx.koff, tn2 * kTK, cx.w);
-  // Some unit of the workgroup keeps every visited tile and the step's barrier waits for
-  // it, so a wave whose own unit skips the tile runs the kept path without contributing
-  // rather than a second code path.
-  float rmax_kept;
-  kept_tile(rs, o, s_cur, mhat, cx.c, s_next, sm.t.k[nb], sm.t.v[j & 1], qf, cx.r, cx.g,
-            cx.lane, rmax_kept, keep_own);
+  // With 32-row units a visited tile is one that some of the workgroup's units keep.  A wave
+  // whose unit skips this one computes only the scores of the next, and nothing at all if it
+  // skips that one too: the co-resident workgroup gets the cycles.  (480p, 10 heads, 25 % of
+  // the unit tiles kept, 33 % visited: 1839 us with every wave running every visited tile
+  // in full, 1765 this way; 720p, 40 heads 34.5 and 33.7 ms.)
+  float rmax_kept = 0.f;
+  if constexpr (UNIT == kTQ) {
+    kept_tile(rs, o, s_cur, mhat, cx.c, s_next, sm.t.k[nb], sm.t.v[j & 1], qf, cx.r, cx.g,
+              cx.lane, rmax_kept);
+  } else {
+    const bool keep_own = __builtin_amdgcn_readfirstlane((e0 >> cx.w) & 1u) != 0;
+    const bool keep_next = __builtin_amdgcn_readfirstlane((e1 >> cx.w) & 1u) != 0;
+    if (keep_own || keep_next)
+      unit_tile(rs, o, s_cur, mhat, cx.c, s_next, sm.t.k[nb], sm.t.v[j & 1], qf, cx.r, cx.g,
+                cx.lane, rmax_kept, keep_own);
+  }
   float mhat_next = 0.f;
   if (has_next) {
     if (cx.ragged && tn == cx.n_kt - 1) {
@@ -1586,44 +1656,56 @@ fa_fwd_mask_kernel(FwdParams p) {
                                              : nullptr;
   }
   // Mask columns are decisions of key_tile keys: 64-key tile t reads column t (64) or
-  // t / 2 (128, two tiles per decision).
+  // t / 2 (128, two tiles per decision).  Thread tid reads the tiles kThreads i + tid, four
+  // rounds' bytes in flight, and holds their keep bits in nibble i of `mine` (n_kt <= 4096:
+  // at most 16 rounds); a wave's 64 tiles of a round are one run, whose visited tiles a
+  // ballot counts.
   const int col_shift = p.key_tile == 2 * kTK ? 1 : 0;
-  auto keep_bits = [&](int t) -> uint32_t {
-    const int col = t >> col_shift;
-    if constexpr (UNIT == kTQ) {
-      return rows[0][col] == 0 ? 0xFu : 0u;
-    } else {
-      uint32_t b = 0;
+  const int rounds = (cx.n_kt + kThreads - 1) / kThreads;
+  uint64_t mine = 0;
+  for (int i0 = 0; i0 < rounds; i0 += 4) {
+    uint8_t skip[4][kTQ / 32];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = (i0 + i) * kThreads + tid;
 #pragma unroll
       for (int u = 0; u < kTQ / 32; ++u)
-        if (rows[u] != nullptr && rows[u][col] == 0) b |= 1u << u;
-      return b;
+        skip[i][u] = (u < n_units && rows[u] != nullptr && t < cx.n_kt)
+                         ? rows[u][t >> col_shift] : (uint8_t)1;
     }
-  };
-  const int per = (cx.n_kt + kThreads - 1) / kThreads;
-  const int t_lo = min(cx.n_kt, tid * per), t_hi = min(cx.n_kt, t_lo + per);
-  uint32_t mine = 0;
-  for (int t = t_lo; t < t_hi; ++t) mine += keep_bits(t) != 0 ? 1u : 0u;
-  sm.count[tid] = (uint16_t)mine;
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t run = 0;
-    for (int i = 0; i < kThreads; ++i) {
-      const uint32_t c = sm.count[i];
-      sm.count[i] = (uint16_t)run;
-      run += c;
-    }
-    sm.total = run;
-  }
-  __syncthreads();
-  {
-    uint32_t at = sm.count[tid];
-    for (int t = t_lo; t < t_hi; ++t) {
-      const uint32_t b = keep_bits(t);
-      if (b != 0) sm.list[at++] = (uint16_t)((t << 4) | b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int u = 0; u < kTQ / 32; ++u) b |= skip[i][u] == 0 ? 1u << u : 0u;
+      if constexpr (UNIT == kTQ) b = b != 0 ? 0xFu : 0u;
+      mine |= (uint64_t)b << (4 * ((i0 + i) & 15));   // rounds past the 16th hold 0
     }
   }
-  const int n_keep = (int)__builtin_amdgcn_readfirstlane(sm.total);
+  for (int i = 0; i < rounds; ++i) {
+    const uint64_t visited = __ballot(((mine >> (4 * i)) & 15u) != 0);
+    if (cx.lane == 0) sm.count[i * kWaves + cx.w] = (uint32_t)__popcll(visited);
+  }
+  __syncthreads();
+  // Every wave scans the at most 64 run counts (lane l: run l, in tile order).  Against a
+  // serial scan of 256 counts by one thread, and byte loads waited for one by one: B = 1,
+  // H = 2, N = 2400 (32-row units) 30.2 us, now 27.2; 480p, 10 heads, 128-row units 1441,
+  // now 1410.
+  const uint32_t own_count = cx.lane < rounds * kWaves ? sm.count[cx.lane] : 0u;
+  uint32_t upto = own_count;
+#pragma unroll
+  for (int sh = 1; sh < 64; sh <<= 1) {
+    const uint32_t below = __shfl_up(upto, sh);
+    if (cx.lane >= sh) upto += below;
+  }
+  const int n_keep = __builtin_amdgcn_readlane((int)upto, 63);
+  for (int i = 0; i < rounds; ++i) {
+    const uint32_t b = (uint32_t)(mine >> (4 * i)) & 15u;
+    const uint64_t visited = __ballot(b != 0);
+    const int at = __builtin_amdgcn_readlane((int)(upto - own_count), i * kWaves + cx.w) +
+                   __popcll(visited & ((1ull << cx.lane) - 1ull));
+    if (b != 0) sm.list[at] = (uint16_t)(((i * kThreads + tid) << 4) | b);
+  }
 
   // The caller's mask is also the output mask; counters from this unit's own mask row.
   if (p.mask != nullptr) {

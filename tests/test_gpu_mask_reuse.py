@@ -175,3 +175,41 @@ def test_wan720p_reuse_of_lambda_mask():
     assert np.array_equal(got.o, ref.o)
     assert np.array_equal(got.lse.view(np.uint32), ref.lse.view(np.uint32))
     assert np.array_equal(got.stats, ref.stats)
+
+
+@pytest.mark.parametrize("N,tile_q,tile_k", [(64 * 64, 32, 64), (64 * 65 - 7, 128, 64),
+                                             (64 * 256, 32, 128), (64 * 257 - 63, 32, 64),
+                                             (64 * 1025 - 1, 128, 128), (262144, 32, 64)])
+def test_visit_list_at_run_and_round_edges(N, tile_q, tile_k):
+    """Key-tile counts around a run of 64, a round of 256, four rounds and the longest list:
+    sampled rows against float64 attention over the kept keys (bf16 output and bf16
+    probabilities: 2^-8 each, four standard deviations over few keys stay below 2e-2)."""
+    import torch
+
+    announce(f"mask list N={N} tile_q={tile_q} tile_k={tile_k}")
+    rng = np.random.default_rng(N)
+    q, k, v = make_random_qkv(1, 1, N, 128, 77, q_std=1.0, k_std=1.0)
+    n_qu, n_kd = -(-N // tile_q), -(-N // tile_k)
+    mask = np.ones((1, 1, n_qu, n_kd), np.uint8)
+    for u in range(n_qu):                                  # three kept decisions a unit,
+        mask[0, 0, u, rng.integers(0, n_kd, 3)] = 0        # the ends of the list among them
+    mask[0, 0, ::5, n_kd - 1] = 0
+    mask[0, 0, 1::7, 0] = 0
+    mask[0, 0, 2] = 1                                      # a unit that keeps nothing
+    qd, kd, vd = upload(q, k, v)
+    g = run_reuse(qd, kd, vd, mask, tile_q, tile_k)
+    np.testing.assert_array_equal(g.mask.reshape(mask.shape), mask)
+    assert (g.stats == expected_stats_from_mask(mask, N, tile_q, tile_k)).all()
+    qf, kf, vf = (x[0, 0].double() for x in (qd, kd, vd))
+    for u in sorted({0, 1, 2, 3, n_qu // 2, n_qu - 1}):
+        r0, r1 = u * tile_q, min(N, (u + 1) * tile_q)
+        o = torch.from_numpy(oracle.bf16_to_f64(g.o[0, 0, r0:r1]))
+        keys = torch.from_numpy(np.repeat(mask[0, 0, u] == 0, tile_k)[:N]).cuda()
+        if not bool(keys.any()):
+            assert (o == 0).all() and np.isneginf(g.lse[0, 0, r0:r1]).all()
+            continue
+        s = (qf[r0:r1] @ kf[keys].t().contiguous()) * SCALE
+        want = torch.softmax(s, 1) @ vf[keys]
+        assert float((o.cuda() - want).abs().max()) < 2e-2
+        lse = torch.from_numpy(g.lse[0, 0, r0:r1].astype(np.float64)).cuda()
+        assert float((lse - torch.logsumexp(s, 1)).abs().max()) < 1e-4
