@@ -226,8 +226,9 @@ int dsattn_scatter_rows(const void* src, void* dst, const int32_t* index, int BH
 
 /*
  * Workspace, in bytes, that dsattn_attn_fwd_reordered needs for a [B][H][N][d] problem
- * (with_lse != 0 when lse_out will be requested): reordered copies of q, k, v and o
- * (and of the LSE).  0 for an empty problem.
+ * (with_lse != 0 when lse_out will be requested): four arrays the size of q (and one the
+ * size of the LSE), of which k and v in visit order are kept there; queries and outputs
+ * are read and written in place.  0 for an empty problem.
  */
 size_t dsattn_reordered_workspace_bytes(int B, int H, int N, int d, int with_lse);
 

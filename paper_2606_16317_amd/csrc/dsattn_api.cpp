@@ -201,8 +201,9 @@ int finish_empty(const dsattn_args& a) {
   return DSATTN_OK;
 }
 
-// Enqueue the attention kernels of a checked, non-empty problem.
-int launch_attention(const dsattn_args& a, const Request& rq) {
+// Enqueue the attention kernels of a checked, non-empty problem.  q_row: null, or the gather
+// map of the queries (see FwdParams); the caller has then cleared the counters already.
+int launch_attention(const dsattn_args& a, const Request& rq, const int32_t* q_row = nullptr) {
   const long long bh = (long long)a.B * (long long)a.H;
   dsattn::FwdParams p;
   p.q = static_cast<const uint16_t*>(a.q);
@@ -230,8 +231,9 @@ int launch_attention(const dsattn_args& a, const Request& rq) {
   p.q_scales = q8 ? a.q_scales : nullptr;
   p.k_scales = q8 ? a.k_scales : nullptr;
   if (q8) p.q = p.k = nullptr;
+  p.q_row = q_row;
 
-  if (p.stats != nullptr &&
+  if (p.stats != nullptr && q_row == nullptr &&
       dsattn::launch_zero_u64(p.stats, (int)(bh * 4), a.stream) != hipSuccess)
     return fail(DSATTN_ELAUNCH, "zero-fill launch failed");
   const hipError_t e = dsattn::launch_fa_fwd(rq.rule, a.tile_q, p, (int)bh, a.stream);
@@ -521,10 +523,9 @@ int reordered(const dsattn_args* args, const int32_t* q_index, const int32_t* kv
     return fail(DSATTN_EINVAL, "workspace too small: %zu bytes given, %zu needed", workspace_size, need);
   }
 
-  // The gathers read q, k, v and the index arrays into the workspace, the kernel reads
-  // and writes the workspace while writing mask_out and stats_out, and the scatters read
-  // the workspace and q_index into o and lse_out: the workspace must be disjoint from
-  // every argument buffer, and the index arrays from everything written.
+  // The gathers read k, v and kv_index into the workspace, the kernel reads that, q and
+  // q_index while writing every output: the workspace must be disjoint from every argument
+  // buffer, and the index arrays from everything written.
   const CallSpans c = call_spans(a);
   const Span ws_span = span("workspace", workspace, need);
   const Span idx[] = {span("q_index", q_index, (size_t)a.N * 4),
@@ -538,31 +539,18 @@ int reordered(const dsattn_args* args, const int32_t* q_index, const int32_t* kv
     for (const Span& w : c.out)
       if (overlap(w, i)) return fail(DSATTN_EINVAL, "%s must not overlap %s", w.name, i.name);
   }
+  // Keys and values are copied into visit order (every query tile reads them again); each
+  // query is read once and each output row written once, in place, through q_index.
   const int bh = a.B * a.H;
   const size_t slice = round_up((size_t)bh * (size_t)a.N * (size_t)a.d * 2);
   char* ws = static_cast<char*>(workspace);
-  dsattn_args r = a;  // the same problem over the reordered sequence
-  r.q = ws;
-  r.k = ws + slice;
-  r.v = ws + 2 * slice;
-  r.o = ws + 3 * slice;
-  r.lse_out = with_lse ? reinterpret_cast<float*>(ws + 4 * slice) : nullptr;
-  const int row = a.d * 2;
-  const struct {
-    const void* src;
-    const void* dst;
-    const int32_t* index;
-  } gathers[] = {{a.q, r.q, q_index}, {a.k, r.k, kv_index}, {a.v, r.v, kv_index}};
-  for (const auto& g : gathers) {
-    const hipError_t e = dsattn::launch_gather_rows(g.src, const_cast<void*>(g.dst), g.index, bh,
-                                                    a.N, row, true, a.stream);
-    if (e != hipSuccess) return fail(DSATTN_ELAUNCH, "gather launch failed: %s", hipGetErrorString(e));
-  }
-  if ((rc = launch_attention(r, rq)) != DSATTN_OK) return rc;
-  hipError_t e = dsattn::launch_scatter_rows(r.o, a.o, q_index, bh, a.N, row, true, a.stream);
-  if (e == hipSuccess && with_lse)
-    e = dsattn::launch_scatter_rows(r.lse_out, a.lse_out, q_index, bh, a.N, 4, false, a.stream);
-  if (e != hipSuccess) return fail(DSATTN_ELAUNCH, "scatter launch failed: %s", hipGetErrorString(e));
+  dsattn_args r = a;
+  r.k = ws;
+  r.v = ws + slice;
+  const hipError_t e = dsattn::launch_gather_kv(a.k, a.v, ws, ws + slice, kv_index, bh, a.N,
+                                                a.d * 2, a.stats_out, a.stream);
+  if (e != hipSuccess) return fail(DSATTN_ELAUNCH, "gather launch failed: %s", hipGetErrorString(e));
+  if ((rc = launch_attention(r, rq, q_index)) != DSATTN_OK) return rc;
   g_last_error.clear();
   return DSATTN_OK;
 }

@@ -678,6 +678,20 @@ __device__ __forceinline__ bool row_keeps_cached(const RowState& rs, float m_hat
     return !(m_hat - rs.m_true < thr);
 }
 
+// Row of q, o and lse that query `qrow` stands for: its entry of the gather map p.q_row
+// (GATHER; N or more where that lies outside the sequence), or itself.  (A compile-time
+// choice: a branch on the pointer cost a call of 36 us 0.5 us.)
+template <bool GATHER>
+__device__ __forceinline__ int query_row(const FwdParams& p, int qrow, bool valid, bool& there) {
+  there = valid;
+  if constexpr (GATHER) {
+    const int row = valid ? p.q_row[qrow] : 0;
+    there = valid && (uint32_t)row < (uint32_t)p.N;
+    return row;
+  }
+  return qrow;
+}
+
 // Per-thread constants of the key-tile loop.
 struct LoopCtx {
   __amdgpu_buffer_rsrc_t krs;   // K / V of this head as buffer resources
@@ -724,14 +738,17 @@ __device__ __forceinline__ int key_tile_or_past(int s, const LoopCtx& cx) {
 // Epilogue of one lane: renormalise O over the kept keys, store it as bf16, and the
 // natural-log LSE of the row over its kept keys.  A row whose unit kept no key tile
 // (possible only with a reused mask) gets zeros and -inf.
+template <bool GATHER>
 __device__ __forceinline__ void store_rows(const FwdParams& p, const f32x16 (&o)[4],
                                            const RowState& rs, const LoopCtx& cx,
                                            size_t head_off, int bh, int qrow) {
   const float l_row = half_sum(rs.l_half);
   const bool any = l_row > 0.f;
   const float inv = any ? 1.0f / l_row : 0.f;
-  if (cx.valid) {
-    uint16_t* orow = p.o + head_off + (size_t)qrow * kD;
+  bool there;
+  const int row = query_row<GATHER>(p, qrow, cx.valid, there);
+  if (there) {
+    uint16_t* orow = p.o + head_off + (size_t)row * kD;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -743,7 +760,7 @@ __device__ __forceinline__ void store_rows(const FwdParams& p, const f32x16 (&o)
             __builtin_bit_cast(u32x2, h);
       }
     if (p.lse != nullptr && cx.g == 0)
-      p.lse[(size_t)bh * cx.N + qrow] =
+      p.lse[(size_t)bh * cx.N + row] =
           any ? (rs.m_ref + log2_fast(l_row)) * 0.69314718055994530942f : -__builtin_inff();
   }
 }
@@ -1367,7 +1384,7 @@ __device__ __forceinline__ void half_tile_step(int j, const f32x16 (&s_cur)[2],
 // on the scaled fp8 MFMA; everything after S is the same as with bf16 Q and K.
 // BC: keys per skip decision: 64 (one tile), 128 (two tiles) or 32 (half a tile); 32
 // walks keys in ascending order only.
-template <int RULE, int UNIT, int ORDER, bool Q8, int BC = kTK>
+template <int RULE, int UNIT, int ORDER, bool Q8, int BC, bool GATHER>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2))) void
 fa_fwd_kernel(FwdParams p) {
@@ -1461,12 +1478,14 @@ fa_fwd_kernel(FwdParams p) {
                  : 0u;
     qf.sc = (qs >> (8 * cx.g)) & 0x00ff00ffu;
   } else {
+    bool there;
+    const int src = query_row<GATHER>(p, qrow, cx.valid, there);
     // Q^T B-operand fragments: d = 16 s + 8 g + (0..7) of this lane's query row.
     const uint16_t* qb = p.q + head_off;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      u32x4 x = cx.valid
-                    ? *reinterpret_cast<const u32x4*>(qb + (size_t)qrow * kD + 16 * s + 8 * cx.g)
+      u32x4 x = there
+                    ? *reinterpret_cast<const u32x4*>(qb + (size_t)src * kD + 16 * s + 8 * cx.g)
                     : u32x4{0, 0, 0, 0};
       qf[s] = __builtin_bit_cast(bf16x8, x);
     }
@@ -1535,7 +1554,7 @@ fa_fwd_kernel(FwdParams p) {
     }
   }
 
-  store_rows(p, o, rs, cx, head_off, bh, qrow);
+  store_rows<GATHER>(p, o, rs, cx, head_off, bh, qrow);
   // One set of counters per decision unit (the workgroup's tile, or each wave's rows).
   if (p.stats != nullptr && (UNIT == kTQ ? cx.w == 0 : true) && cx.lane == 0 &&
       cx.rows_valid > 0) {
@@ -1609,7 +1628,7 @@ __device__ __forceinline__ void mask_tile_step(int j, int n_keep, const f32x16 (
   e2 = __builtin_amdgcn_readfirstlane(e3_raw);
 }
 
-template <int UNIT>
+template <int UNIT, bool GATHER>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2))) void
 fa_fwd_mask_kernel(FwdParams p) {
@@ -1748,12 +1767,15 @@ fa_fwd_mask_kernel(FwdParams p) {
     const int t0 = list_tile(sm, 0);
     load_tile_lds(sm.t.k[0], cx.krs, cx.koff, t0 * kTK, cx.w);
     load_tile_lds(sm.t.v[0], cx.vrs, cx.voff, t0 * kTK, cx.w);
-    const uint16_t* qb = p.q + head_off;
     bf16x8 qf[8];
+    bool there;
+    const int src = query_row<GATHER>(p, qrow, cx.valid, there);
+    // Q^T B-operand fragments: d = 16 s + 8 g + (0..7) of this lane's query row.
+    const uint16_t* qb = p.q + head_off;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      u32x4 x = cx.valid
-                    ? *reinterpret_cast<const u32x4*>(qb + (size_t)qrow * kD + 16 * s + 8 * cx.g)
+      u32x4 x = there
+                    ? *reinterpret_cast<const u32x4*>(qb + (size_t)src * kD + 16 * s + 8 * cx.g)
                     : u32x4{0, 0, 0, 0};
       qf[s] = __builtin_bit_cast(bf16x8, x);
     }
@@ -1777,7 +1799,7 @@ fa_fwd_mask_kernel(FwdParams p) {
         mask_tile_step<UNIT>(j + 1, n_keep, sb, sa, mhat, rs, o, qf, sm, cx, e0, e1, e2);
     }
   }
-  store_rows(p, o, rs, cx, head_off, bh, qrow);
+  store_rows<GATHER>(p, o, rs, cx, head_off, bh, qrow);
 }
 
 __global__ void zero_u64_kernel(uint64_t* __restrict__ p, int n) {
@@ -1789,67 +1811,24 @@ __global__ void zero_u64_kernel(uint64_t* __restrict__ p, int n) {
 
 namespace {
 
-template <int UNIT, int ORDER, bool Q8 = false>
-hipError_t launch_unit(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
+// The rule of a checked request as a template parameter; the dense rule keeps every tile, so
+// that the visit order changes nothing but the rounding of the sums: it always walks
+// ascending.
+template <int UNIT, int ORDER, bool Q8, int BC, bool GATHER>
+hipError_t launch_rule(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
   const dim3 block(kThreads);
   switch (rule) {
     case kRuleDense:
-      // Every tile is kept, so the visit order changes nothing but the rounding of the
-      // sums: the dense kernel always walks ascending.
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDense, UNIT, kOrderAscending, Q8>), grid, block, 0,
-                         stream, p);
-      break;
-    case kRuleBlasst:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleBlasst, UNIT, ORDER, Q8>), grid, block, 0, stream,
-                         p);
-      break;
-    case kRuleDynSparse:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDynSparse, UNIT, ORDER, Q8>), grid, block, 0,
-                         stream, p);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <int UNIT, bool Q8, int ORDER>
-hipError_t launch_pair(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
-  const dim3 block(kThreads);
-  switch (rule) {
-    case kRuleDense:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDense, UNIT, kOrderAscending, Q8, 2 * kTK>), grid,
+      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDense, UNIT, kOrderAscending, Q8, BC, GATHER>), grid,
                          block, 0, stream, p);
       break;
     case kRuleBlasst:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleBlasst, UNIT, ORDER, Q8, 2 * kTK>), grid, block, 0,
-                         stream, p);
-      break;
-    case kRuleDynSparse:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDynSparse, UNIT, ORDER, Q8, 2 * kTK>), grid, block,
+      hipLaunchKernelGGL((fa_fwd_kernel<kRuleBlasst, UNIT, ORDER, Q8, BC, GATHER>), grid, block,
                          0, stream, p);
       break;
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <int UNIT, bool Q8>
-hipError_t launch_half(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
-  const dim3 block(kThreads);
-  switch (rule) {
-    case kRuleDense:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDense, UNIT, kOrderAscending, Q8, kTK / 2>), grid,
-                         block, 0, stream, p);
-      break;
-    case kRuleBlasst:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleBlasst, UNIT, kOrderAscending, Q8, kTK / 2>), grid,
-                         block, 0, stream, p);
-      break;
     case kRuleDynSparse:
-      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDynSparse, UNIT, kOrderAscending, Q8, kTK / 2>),
-                         grid, block, 0, stream, p);
+      hipLaunchKernelGGL((fa_fwd_kernel<kRuleDynSparse, UNIT, ORDER, Q8, BC, GATHER>), grid,
+                         block, 0, stream, p);
       break;
     default:
       return hipErrorInvalidValue;
@@ -1857,27 +1836,40 @@ hipError_t launch_half(int rule, const FwdParams& p, dim3 grid, hipStream_t stre
   return hipGetLastError();
 }
 
-template <int UNIT, bool Q8>
+template <int UNIT, bool Q8, bool GATHER>
 hipError_t launch_order(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
-  if (p.key_tile == 2 * kTK) {
-    if (p.key_order == kOrderDiagonal && rule != kRuleDense) {
-      const int chunk = (p.n_qt + kXcds - 1) / kXcds;
-      return launch_pair<UNIT, Q8, kOrderDiagonal>(rule, p,
-                                                   dim3((unsigned)(chunk * kXcds), grid.y),
-                                                   stream);
-    }
-    return launch_pair<UNIT, Q8, kOrderAscending>(rule, p, grid, stream);
-  }
-  if (p.key_tile == kTK / 2) {
-    if (p.key_order != kOrderAscending) return hipErrorInvalidValue;
-    return launch_half<UNIT, Q8>(rule, p, grid, stream);
-  }
   if (p.key_order == kOrderDiagonal && rule != kRuleDense) {
     const int chunk = (p.n_qt + kXcds - 1) / kXcds;
-    return launch_unit<UNIT, kOrderDiagonal, Q8>(rule, p,
-                                                 dim3((unsigned)(chunk * kXcds), grid.y), stream);
+    const dim3 padded((unsigned)(chunk * kXcds), grid.y);
+    if (p.key_tile == 2 * kTK)
+      return launch_rule<UNIT, kOrderDiagonal, Q8, 2 * kTK, GATHER>(rule, p, padded, stream);
+    if (p.key_tile == kTK)
+      return launch_rule<UNIT, kOrderDiagonal, Q8, kTK, GATHER>(rule, p, padded, stream);
+    return hipErrorInvalidValue;   // 32-key decisions walk ascending
   }
-  return launch_unit<UNIT, kOrderAscending, Q8>(rule, p, grid, stream);
+  if (p.key_tile == 2 * kTK)
+    return launch_rule<UNIT, kOrderAscending, Q8, 2 * kTK, GATHER>(rule, p, grid, stream);
+  if (p.key_tile == kTK / 2) {
+    if (p.key_order != kOrderAscending) return hipErrorInvalidValue;
+    return launch_rule<UNIT, kOrderAscending, Q8, kTK / 2, GATHER>(rule, p, grid, stream);
+  }
+  return launch_rule<UNIT, kOrderAscending, Q8, kTK, GATHER>(rule, p, grid, stream);
+}
+
+template <int UNIT, bool GATHER>
+hipError_t launch_format(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
+  if (rule == kRuleMask) {
+    if (p.n_kt > kMaxMaskTiles || p.mask_in == nullptr) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((fa_fwd_mask_kernel<UNIT, GATHER>), grid, dim3(kThreads), 0, stream, p);
+    return hipGetLastError();
+  }
+  if (p.qk_format == kQkMxfp8) {
+    if (p.q8 == nullptr || p.k8 == nullptr || p.q_scales == nullptr || p.k_scales == nullptr ||
+        GATHER)
+      return hipErrorInvalidValue;
+    return launch_order<UNIT, true, false>(rule, p, grid, stream);
+  }
+  return launch_order<UNIT, false, GATHER>(rule, p, grid, stream);
 }
 
 }  // namespace
@@ -1885,25 +1877,12 @@ hipError_t launch_order(int rule, const FwdParams& p, dim3 grid, hipStream_t str
 hipError_t launch_fa_fwd(int rule, int unit_rows, const FwdParams& p, int bh,
                          hipStream_t stream) {
   const dim3 grid((unsigned)p.n_qt, (unsigned)bh);
-  if (rule == kRuleMask) {
-    if (p.n_kt > kMaxMaskTiles || p.mask_in == nullptr) return hipErrorInvalidValue;
-    if (unit_rows == kTQ)
-      hipLaunchKernelGGL((fa_fwd_mask_kernel<kTQ>), grid, dim3(kThreads), 0, stream, p);
-    else if (unit_rows == 32)
-      hipLaunchKernelGGL((fa_fwd_mask_kernel<32>), grid, dim3(kThreads), 0, stream, p);
-    else
-      return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
-  if (p.qk_format == kQkMxfp8) {
-    if (p.q8 == nullptr || p.k8 == nullptr || p.q_scales == nullptr || p.k_scales == nullptr)
-      return hipErrorInvalidValue;
-    if (unit_rows == kTQ) return launch_order<kTQ, true>(rule, p, grid, stream);
-    if (unit_rows == 32) return launch_order<32, true>(rule, p, grid, stream);
-    return hipErrorInvalidValue;
-  }
-  if (unit_rows == kTQ) return launch_order<kTQ, false>(rule, p, grid, stream);
-  if (unit_rows == 32) return launch_order<32, false>(rule, p, grid, stream);
+  if (unit_rows == kTQ)
+    return p.q_row != nullptr ? launch_format<kTQ, true>(rule, p, grid, stream)
+                              : launch_format<kTQ, false>(rule, p, grid, stream);
+  if (unit_rows == 32)
+    return p.q_row != nullptr ? launch_format<32, true>(rule, p, grid, stream)
+                              : launch_format<32, false>(rule, p, grid, stream);
   return hipErrorInvalidValue;
 }
 

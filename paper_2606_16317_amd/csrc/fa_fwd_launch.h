@@ -34,6 +34,10 @@ struct FwdParams {
   const uint8_t* k_scales;
   int key_tile;            // keys per skip decision: 64, or 128 (two 64-key tiles)
   int n_kd;                // ceil(N / key_tile): decisions per row of the mask
+  // Null, or an int32 [N] gather map of the queries: query i is row q_row[i] of q, and its
+  // output and LSE go to that row of o and lse (entries outside [0, N): a zero query, and
+  // nothing stored).  Bf16 only; k and v are in visit order.
+  const int32_t* q_row;
 };
 
 // Enqueue one forward pass over `bh` heads on `stream`; unit_rows (128 or 32) is the

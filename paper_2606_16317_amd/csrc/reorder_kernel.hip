@@ -48,6 +48,28 @@ __global__ __launch_bounds__(kThreads) void move_rows_kernel(const T* __restrict
   }
 }
 
+// The gathers ahead of a reordered attention call in one launch: blockIdx.z 0 moves k, 1
+// v (both [heads][N] rows of per_row 16-byte chunks, same map), and the first block of every
+// head clears that head's four counters.  (Gathers of q, k and v, a fill and a scatter back
+// were five launches around a small call's one.)
+__global__ __launch_bounds__(kThreads) void gather_kv_kernel(
+    const u32x4* __restrict__ k, const u32x4* __restrict__ v, u32x4* __restrict__ k_out,
+    u32x4* __restrict__ v_out, const int32_t* __restrict__ index, int N, int per_row,
+    uint64_t* __restrict__ counters) {
+  if (counters != nullptr && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x < 4)
+    counters[(size_t)blockIdx.y * 4 + threadIdx.x] = 0;
+  const uint32_t c = blockIdx.x * kThreads + threadIdx.x;
+  const uint32_t head_chunks = (uint32_t)N * (uint32_t)per_row;
+  if (c >= head_chunks) return;
+  const uint32_t i = c / (uint32_t)per_row;
+  const uint32_t w = c - i * (uint32_t)per_row;
+  const size_t head = (size_t)blockIdx.y * head_chunks;
+  const uint32_t s = (uint32_t)index[i];
+  const u32x4* src = blockIdx.z == 0 ? k : v;
+  u32x4* dst = blockIdx.z == 0 ? k_out : v_out;
+  dst[head + c] = s < (uint32_t)N ? src[head + (size_t)s * per_row + w] : u32x4{};
+}
+
 template <bool kScatter>
 hipError_t launch(const void* src, void* dst, const int32_t* index, int bh, int N,
                   int row_bytes, bool wide, hipStream_t stream) {
@@ -75,6 +97,19 @@ hipError_t launch_gather_rows(const void* src, void* dst, const int32_t* index, 
 hipError_t launch_scatter_rows(const void* src, void* dst, const int32_t* index, int bh, int N,
                                int row_bytes, bool wide, hipStream_t stream) {
   return launch<true>(src, dst, index, bh, N, row_bytes, wide, stream);
+}
+
+hipError_t launch_gather_kv(const void* k, const void* v, void* k_out, void* v_out,
+                            const int32_t* index, int bh, int N, int row_bytes,
+                            uint64_t* counters, hipStream_t stream) {
+  const int per_row = row_bytes / 16;
+  const uint32_t chunks = (uint32_t)N * (uint32_t)per_row;
+  const dim3 grid((chunks + kThreads - 1) / kThreads, (unsigned)bh, 2);
+  hipLaunchKernelGGL(gather_kv_kernel, grid, dim3(kThreads), 0, stream,
+                     static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
+                     static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), index, N, per_row,
+                     counters);
+  return hipGetLastError();
 }
 
 }  // namespace dsattn

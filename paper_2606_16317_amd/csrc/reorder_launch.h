@@ -18,6 +18,12 @@ hipError_t launch_gather_rows(const void* src, void* dst, const int32_t* index, 
 hipError_t launch_scatter_rows(const void* src, void* dst, const int32_t* index, int bh, int N,
                                int row_bytes, bool wide, hipStream_t stream);
 
+// k_out[b][i] = k[b][index[i]] and the same for v, as launch_gather_rows with `wide`; with
+// counters (uint64 [bh][4], may be null) set to zero as well.
+hipError_t launch_gather_kv(const void* k, const void* v, void* k_out, void* v_out,
+                            const int32_t* index, int bh, int N, int row_bytes,
+                            uint64_t* counters, hipStream_t stream);
+
 }  // namespace dsattn
 
 #endif

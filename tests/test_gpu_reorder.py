@@ -186,6 +186,65 @@ def test_identity_maps_reproduce_the_plain_call_bit_for_bit():
         assert np.array_equal(r.lse.view(np.uint32), p.lse.view(np.uint32))
 
 
+@pytest.mark.parametrize("rule,param,tile_q,tile_k,order,N", [
+    ("dense", 0.0, 128, 64, 0, 129), ("dynsparse_lambda", -4.0, 32, 64, 1, 1000),
+    ("dynsparse_recall", 0.95, 128, 128, 0, 640), ("blasst", 0.05, 128, 32, 0, 65),
+    ("dynsparse_lambda", -4.0, 128, 128, 1, 777), ("mask", 0.0, 32, 64, 0, 1000),
+    ("mask", 0.0, 128, 128, 0, 300)])
+def test_reordered_call_equals_gathers_plain_call_and_scatters(rule, param, tile_q, tile_k,
+                                                               order, N):
+    """Queries read and outputs written in place through q_index have the bits of moving
+    q, k and v first, the plain call, and moving o and the LSE back; entries outside the
+    sequence stand for a zero query and leave their output rows alone."""
+    import ctypes
+
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"reordered in place {rule}={param} tile_q={tile_q} tile_k={tile_k} N={N}")
+    B, H = 2, 2
+    qd, kd, vd = (to_device(x) for x in make_random_qkv(B, H, N, 128, N, q_std=2.0, k_std=2.0))
+    rng = np.random.default_rng(N)
+    qi, ki = rng.permutation(N), rng.permutation(N)
+    qi[5], qi[N - 1], qi[N // 2] = -1, N, 2 ** 31 - 1
+    ki[3] = -7
+    qi, ki = dev_index(qi), dev_index(ki)
+    n_qu, n_kd = -(-N // tile_q), -(-N // tile_k)
+    mask_in = torch.from_numpy((rng.random((B, H, n_qu, n_kd)) < 0.6).astype(np.uint8)).cuda()
+    rule_id = dsa.RULE_MASK if rule == "mask" else RULE_NAMES[rule]
+
+    def outputs():
+        return {"stats_out": torch.full((B * H * 4,), -7, dtype=torch.int64, device="cuda"),
+                "mask_out": torch.full((B * H * n_qu * n_kd,), 7, dtype=torch.uint8,
+                                       device="cuda"),
+                "lse_out": torch.full((B, H, N, 1), 9.0, dtype=torch.float32, device="cuda")}
+
+    plain, o_plain, o_back = outputs(), torch.empty_like(qd), torch.full_like(qd, 3.0)
+    dsa.dsattn_attn_fwd_ex(rule_id, param, *(dsa.dsattn_gather_rows(x, i) for x, i in
+                                             ((qd, qi), (kd, ki), (vd, ki))), o_plain,
+                           tile_q=tile_q, tile_k=tile_k, key_order=order, mask_in=mask_in, **plain)
+    dsa.dsattn_scatter_rows(o_plain, qi, o_back)
+    lse_back = torch.full((B, H, N, 1), 9.0, dtype=torch.float32, device="cuda")
+    dsa.dsattn_scatter_rows(plain["lse_out"], qi, lse_back)
+
+    got, o = outputs(), torch.full_like(qd, 3.0)
+    ws = torch.empty(dsa.dsattn_reordered_workspace_bytes(B, H, N, 128, True), dtype=torch.uint8,
+                     device="cuda")
+    a = dsa.DsAttnArgs(rule_id, param, qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(),
+                       B, H, N, 128, SCALE, tile_q, tile_k,
+                       torch.cuda.current_stream().cuda_stream, got["stats_out"].data_ptr(),
+                       got["mask_out"].data_ptr(), got["lse_out"].data_ptr(), order,
+                       mask_in.data_ptr())
+    rc = dsa.lib().dsattn_attn_fwd_reordered(ctypes.byref(a), qi.data_ptr(), ki.data_ptr(),
+                                             ws.data_ptr(), ws.numel())
+    assert rc == 0, dsa.last_error()
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), o_back.view(torch.int16))
+    assert torch.equal(got["lse_out"], lse_back)
+    assert torch.equal(got["stats_out"], plain["stats_out"])
+    assert torch.equal(got["mask_out"], plain["mask_out"])
+
+
 def test_reordering_raises_sparsity_on_video_inputs():
     """Blocked order gathers spatial neighbours into tiles: on these video-shaped inputs the
     reordered run skips more tiles than the row-major one at the same lambda (the oracle
