@@ -152,6 +152,18 @@ def _check(rc: int, name: str):
 def _shape(q, k, v, o):
     import torch
 
+    # All in order: the common case, in one expression.
+    try:
+        if (q.dtype is k.dtype is v.dtype is o.dtype is torch.bfloat16
+                and q.is_cuda and k.is_cuda and v.is_cuda and o.is_cuda
+                and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
+                and o.is_contiguous()):
+            shape = q.shape
+            if len(shape) == 4 and shape == k.shape == v.shape == o.shape and all(
+                    isinstance(t, torch.Tensor) for t in (q, k, v, o)):
+                return tuple(shape)
+    except AttributeError:
+        pass
     for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
         if not isinstance(t, torch.Tensor):
             raise TypeError(f"{name} must be a torch.Tensor")
@@ -181,10 +193,15 @@ def _ptr(t, numel=None, dtype=None, name="buffer"):
 
 
 def _stream(stream):
+    """Handle of `stream`, or of the current stream of the current device."""
     import torch
 
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # The handle alone: building a torch.cuda.Stream object takes 2.6 us of a 9 us call.
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(
+        torch.cuda.current_device())
 
 
 def _workspace(nbytes, device, stream):
@@ -211,6 +228,8 @@ def _out(q, o):
 def _buffers(B, H, N, stats_out, mask_out=None, lse_out=None, tile_q=TILE_Q, tile_k=TILE_K):
     import torch
 
+    if stats_out is None and mask_out is None and lse_out is None:
+        return None, None, None
     n_qt = -(-N // max(1, tile_q))
     n_kt = -(-N // max(1, tile_k))
     return (_ptr(stats_out, B * H * 4, (torch.int64, torch.uint64), "stats_out"),
