@@ -232,6 +232,7 @@ int launch_attention(const dsattn_args& a, const Request& rq, const int32_t* q_r
   p.k_scales = q8 ? a.k_scales : nullptr;
   if (q8) p.q = p.k = nullptr;
   p.q_row = q_row;
+  p.interleave = false;
 
   if (p.stats != nullptr && q_row == nullptr &&
       dsattn::launch_zero_u64(p.stats, (int)(bh * 4), a.stream) != hipSuccess)

@@ -1384,6 +1384,36 @@ __device__ __forceinline__ void half_tile_step(int j, const f32x16 (&s_cur)[2],
 // on the scaled fp8 MFMA; everything after S is the same as with bf16 Q and K.
 // BC: keys per skip decision: 64 (one tile), 128 (two tiles) or 32 (half a tile); 32
 // walks keys in ascending order only.
+// Head and query tile of this workgroup, from its place (bh, qt) in the grid: the heads are
+// taken eight at a time (what is left over four, two and one at a time) and the g heads of a
+// group interleaved, so that neighbours in dispatch order, which go to different XCDs, hold
+// different heads and the workgroups that share an XCD's L2 share one head's K and V (g = 8;
+// two XCDs a head for g = 4, and so on).  After every 1/g of the query tiles the heads move
+// on by one XCD, so that each XCD gets every head's share of the work.  A permutation of the
+// grid: a tile's g places hold the g heads, rotated.
+//
+// What bounds such launches: workgroups that skip at different rates, or walk different lists
+// of tiles, drift apart in the key loop, and their K and V then come from behind L2.  With two
+// or more heads in flight each XCD streamed all of them.  Measured as grid order -> this, us:
+// mask reuse 480p (N = 32760), 10 heads, 32-row units, 25 % kept 1657 -> 1586; 40 heads,
+// 128-row units 5160 -> 5047; N = 75600, 5 heads 3524 -> 3411; MX-FP8 480p, 10 heads,
+// lambda -8 3798 -> 3616.  Groups of 8 without the rotation gain as much on even heads and
+// lose up to 6 % where heads skip differently.  Where the line lies: interleaves_heads().
+__device__ __forceinline__ void interleave_heads(int n_qt, int& bh, int& qt) {
+  const int heads = (int)gridDim.y;
+  int base = 0, log_g = 3;
+  for (; log_g > 0; --log_g) {
+    const int end = base + (((heads - base) >> log_g) << log_g);
+    if (bh < end) break;
+    base = end;
+  }
+  base += ((bh - base) >> log_g) << log_g;
+  const int g = 1 << log_g;
+  const int place = (bh - base) * n_qt + qt;
+  qt = place >> log_g;
+  bh = base + ((place + qt / ((n_qt + g - 1) >> log_g)) & (g - 1));
+}
+
 template <int RULE, int UNIT, int ORDER, bool Q8, int BC, bool GATHER>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2))) void
@@ -1407,7 +1437,9 @@ fa_fwd_kernel(FwdParams p) {
     qt = (int)(blockIdx.x % kXcds) * chunk + (int)(blockIdx.x / kXcds);
     if (qt >= p.n_qt) return;
   }
-  const int bh = blockIdx.y;
+  int bh = blockIdx.y;
+  if constexpr (Q8 && ORDER == kOrderAscending)
+    if (p.interleave) interleave_heads(p.n_qt, bh, qt);
   const int N = p.N;
   const size_t head_off = (size_t)bh * (size_t)N * kD;
 
@@ -1636,8 +1668,9 @@ fa_fwd_mask_kernel(FwdParams p) {
   __shared__ __attribute__((aligned(16))) MaskSmem sm;
 
   const int tid = threadIdx.x;
-  const int qt = blockIdx.x;
-  const int bh = blockIdx.y;
+  int qt = blockIdx.x;
+  int bh = blockIdx.y;
+  if (p.interleave) interleave_heads(p.n_qt, bh, qt);
   const int N = p.N;
   const size_t head_off = (size_t)bh * (size_t)N * kD;
 
@@ -1856,8 +1889,28 @@ hipError_t launch_order(int rule, const FwdParams& p, dim3 grid, hipStream_t str
   return launch_rule<UNIT, kOrderAscending, Q8, kTK, GATHER>(rule, p, grid, stream);
 }
 
+// Whether a launch interleaves its heads (see interleave_heads).  Up to kResident workgroups
+// are all in flight at once, and there the order gained nothing (mask reuse, 3 heads of 122
+// query tiles: 220.0 us against 221.9).  Mask reuse gained 2 to 4 % at every size above that.
+// MX-FP8 rules gained 0 to 8 % with the threshold at or below lambda = -7.5 or tau = 0.01
+// (480p, 40 heads, lambda -8: 15.21 -> 14.60 ms; N = 75600, 10 heads: 18.95 -> 18.92; at worst
+// 0.6 % lost); with higher thresholds, where most tiles are skipped, heads differ more and 40
+// heads of 480p lost 0.5 % (lambda -7) and 2 % (-6).  The bf16 rules, whose key loop takes
+// longer, moved by -2 to +3 % at lambda -6 to -9 with no clear gain: grid order.
+constexpr long long kResident = 512;          // workgroups in flight: two on each of 256 CUs
+bool interleaves_heads(int rule, const FwdParams& p, dim3 grid) {
+  if (grid.y < 2 || (long long)grid.x * grid.y <= kResident) return false;
+  if (rule == kRuleMask) return true;
+  if (p.qk_format != kQkMxfp8) return false;
+  if (rule == kRuleDynSparse) return p.thr <= -10.82f;   // lambda <= -7.5, in log2 units
+  if (rule == kRuleBlasst) return p.thr <= -6.64f;       // tau <= 0.01
+  return true;                                           // dense
+}
+
 template <int UNIT, bool GATHER>
-hipError_t launch_format(int rule, const FwdParams& p, dim3 grid, hipStream_t stream) {
+hipError_t launch_format(int rule, const FwdParams& params, dim3 grid, hipStream_t stream) {
+  FwdParams p = params;
+  p.interleave = interleaves_heads(rule, p, grid);
   if (rule == kRuleMask) {
     if (p.n_kt > kMaxMaskTiles || p.mask_in == nullptr) return hipErrorInvalidValue;
     hipLaunchKernelGGL((fa_fwd_mask_kernel<UNIT, GATHER>), grid, dim3(kThreads), 0, stream, p);

@@ -38,6 +38,7 @@ struct FwdParams {
   // output and LSE go to that row of o and lse (entries outside [0, N): a zero query, and
   // nothing stored).  Bf16 only; k and v are in visit order.
   const int32_t* q_row;
+  bool interleave;         // the launch interleaves its heads (set by launch_fa_fwd)
 };
 
 // Enqueue one forward pass over `bh` heads on `stream`; unit_rows (128 or 32) is the
