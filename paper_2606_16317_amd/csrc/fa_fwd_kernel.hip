@@ -488,8 +488,6 @@ __device__ __forceinline__ void kept_tile(RowState& rs, f32x16 (&o)[4], const f3
   rs.l_half += psum;
 }
 
-// Kept tile j: softmax of S_j interleaved with the 16 MFMAs of S_{j+1} = K_{j+1} Q^T,
-// then O += P V_j.  MFMA operands are read from LDS two MFMAs ahead.
 // Visited tile j of a reused mask with 32-row units: as kept_tile when the wave's unit keeps
 // tile j (`contribute`, uniform); otherwise S_{j+1} only, the softmax slots running on
 // exp2(-inf) = 0 and the P V phase left out.  (Branching around the P V phase alone keeps
@@ -527,6 +525,10 @@ __device__ __forceinline__ void unit_tile(RowState& rs, f32x16 (&o)[4], const f3
     }
     sched_fence();
   }
+  // Only the branch below reads them: without this the compiler sinks the exponentials into
+  // it, after the MFMAs that should hide them.
+#pragma unroll
+  for (int b = 0; b < 3; ++b) pin_here(pf[b]);
   if (contribute) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -1633,7 +1635,9 @@ __device__ __forceinline__ void mask_tile_step(int j, int n_keep, const f32x16 (
   // whose unit skips this one computes only the scores of the next, and nothing at all if it
   // skips that one too: the co-resident workgroup gets the cycles.  (480p, 10 heads, 25 % of
   // the unit tiles kept, 33 % visited: 1839 us with every wave running every visited tile
-  // in full, 1765 this way; 720p, 40 heads 34.5 and 33.7 ms.)
+  // in full, 1765 this way; 720p, 40 heads 34.5 and 33.7 ms.  A launch that leaves the chip
+// idle, 2 heads of N = 4092 with 40 % kept: 53.4 us while the exponentials sank behind the
+// branch on keep_own, 49.9 with them pinned under the Q K^T MFMAs.)
   float rmax_kept = 0.f;
   if constexpr (UNIT == kTQ) {
     kept_tile(rs, o, s_cur, mhat, cx.c, s_next, sm.t.k[nb], sm.t.v[j & 1], qf, cx.r, cx.g,
