@@ -29,20 +29,19 @@ constexpr int kThreads = 256;
 constexpr int kChunks = 4;               // 8-value chunks per thread
 constexpr int kChunkValues = 8;
 
-// E4M3 codes of four finite floats (byte i from y[i]), rounded to nearest with ties to
-// the even code, saturating at 448 (0x7e).  The conversion keeps the sign of values that
-// round to zero; the byte arithmetic after it turns 0x80 into +0 (bit 7 of `nz` is set
-// where a byte's low seven bits are not all zero).
-__device__ __forceinline__ uint32_t e4m3_codes(const float* y) {
+// E4M3 codes of four floats (byte i from y[i]), rounded to nearest with ties to the even
+// code, magnitudes above 448 and NaN to 448 (0x7e), with the signs in bits 7, 15, 23 and 31 of
+// `signs` except where the value rounds to zero: +0 (bit 7 of `nz` is set where a byte of the
+// magnitudes' codes is not zero).
+__device__ __forceinline__ uint32_t e4m3_codes(const float* y, uint32_t signs) {
   float c[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) c[i] = __builtin_amdgcn_fmed3f(y[i], -448.0f, 448.0f);
+  for (int i = 0; i < 4; ++i) c[i] = fminf(fabsf(y[i]), 448.0f);
   int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
   w = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
-  const uint32_t codes = (uint32_t)w;
-  const uint32_t low = codes & 0x7f7f7f7fu;
+  const uint32_t low = (uint32_t)w;
   const uint32_t nz = low + 0x7f7f7f7fu;
-  return low | (codes & nz & 0x80808080u);
+  return low | (signs & nz & 0x80808080u);
 }
 
 // Maximum over the four lanes of an aligned quad.
@@ -67,7 +66,8 @@ __device__ __forceinline__ void quantize_chunk(const u32x4& w, const float (&sh)
     x[2 * j] = bf16_lo(w[j]);
     x[2 * j + 1] = bf16_hi(w[j]);
   }
-  // Bit pattern of max |x|: magnitudes of finite floats order as integers.
+  // Bit pattern of max |x| over the block's numbers: magnitudes order as integers, and a NaN
+  // counts as zero.
   uint32_t amax;
   if constexpr (SHIFT) {
     float m = 0.f;
@@ -83,16 +83,38 @@ __device__ __forceinline__ void quantize_chunk(const u32x4& w, const float (&sh)
     for (int j = 1; j < 4; ++j)
       m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
     amax = (uint32_t)max(m[0], m[1]) << 16;
+    if (amax > 0x7f800000u) {          // rare: a NaN among them
+      amax = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t lo = w[j] << 16 & 0x7fff0000u, hi = w[j] & 0x7fff0000u;
+        amax = max(amax, max(lo <= 0x7f800000u ? lo : 0u, hi <= 0x7f800000u ? hi : 0u));
+      }
+    }
   }
   amax = quad_max(amax);
   // floor(log2 amax) - 8 + 127 is the biased exponent minus 8; zero and tiny blocks (and
-  // subnormal maxima, whose biased exponent is 0) clamp to code 0.
-  const int e = (int)(amax >> 23) - 8;
-  scode = (uint32_t)min(254, max(0, e));
+  // subnormal maxima, whose biased exponent is 0) clamp to code 0.  Blocks with an infinity
+  // take the scale 2^-9.
+  scode = amax >= 0x7f800000u ? 118u : (uint32_t)max(0, (int)(amax >> 23) - 8);
   const float inv = __uint_as_float((254u - scode) << 23);   // 2^(127 - scode), exact
 #pragma unroll
   for (int i = 0; i < kChunkValues; ++i) x[i] *= inv;
-  out = u32x2{e4m3_codes(x), e4m3_codes(x + 4)};
+  // The signs: bytes 1 and 3 of the words of two values each, or the top bytes of the floats.
+  uint32_t signs[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if constexpr (SHIFT) {
+      const uint32_t a = __builtin_amdgcn_perm(__float_as_uint(x[4 * i + 1]),
+                                               __float_as_uint(x[4 * i]), 0x0c0c0703u);
+      const uint32_t b = __builtin_amdgcn_perm(__float_as_uint(x[4 * i + 3]),
+                                               __float_as_uint(x[4 * i + 2]), 0x0c0c0703u);
+      signs[i] = b << 16 | a;
+    } else {
+      signs[i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x07050301u);
+    }
+  }
+  out = u32x2{e4m3_codes(x, signs[0]), e4m3_codes(x + 4, signs[1])};
 }
 
 // blockIdx.y (in steps of gridDim.y) is the group of rows that shares a shift vector (one

@@ -131,6 +131,50 @@ def test_quantize_every_bf16_pattern_and_run_edges(rows, row_len):
         np.testing.assert_array_equal(codes, want_c)
 
 
+def quantize_non_finite(x):
+    """Codes and exponents of float64 rows with infinities and NaN: a NaN counts as zero in its
+    block's maximum and saturates with its sign (0x7e or 0xfe); a block with an infinity takes
+    the scale 2^-9 (code 118), and what exceeds 448 / 2^9 saturates."""
+    num = np.where(np.isnan(x), 0.0, x)
+    blocks = num.reshape(-1, 32)
+    inf = np.isinf(blocks).any(1)
+    with_inf = np.clip(blocks * 512.0, -448.0, 448.0)        # its maximum is 448: code 127
+    codes, scales = quantize_mxfp8(np.where(inf[:, None], with_inf, blocks))
+    scales = np.where(inf, 118, scales.reshape(-1)).astype(np.uint8)
+    codes = codes.reshape(x.shape)
+    nan = np.where(np.signbit(x), 0xfe, 0x7e).astype(np.uint8)
+    return np.where(np.isnan(x), nan, codes), scales.reshape(*x.shape[:-1], x.shape[-1] // 32)
+
+
+@pytest.mark.parametrize("shifted", [False, True])
+def test_quantize_non_finite_values(shifted):
+    """Every NaN and infinity pattern of bf16 among ordinary values, alone in a block of zeros
+    and in a block of its own kind: the other values of a block with a NaN keep their codes."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"mxfp8 non-finite shifted={shifted}")
+    pats = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    odd = pats[(pats & 0x7f80) == 0x7f80]                    # 254 NaN patterns, two infinities
+    rng = np.random.default_rng(8)
+    rows = bf16_bits(rng.standard_normal((3 * odd.size, 128)).astype(np.float32))
+    rows[np.arange(odd.size), rng.integers(0, 128, odd.size)] = odd
+    rows[odd.size:2 * odd.size] = 0
+    rows[odd.size + np.arange(odd.size), rng.integers(0, 128, odd.size)] = odd
+    rows[2 * odd.size:, 32:64] = odd[rng.integers(0, odd.size, (odd.size, 32))]
+    bits = rows.reshape(1, 1, -1, 128)
+    x = bf16_to_f64(bits)
+    shift = None
+    if shifted:
+        shift = rng.standard_normal((1, 1, 128)).astype(np.float32)
+        x = (x.astype(np.float32) - shift[:, :, None]).astype(np.float64)
+        shift = torch.from_numpy(shift).cuda()
+    codes, scales = dsa.dsattn_quantize_mxfp8(to_device(bits), shift=shift)
+    want_c, want_s = quantize_non_finite(x)
+    np.testing.assert_array_equal(scales.cpu().numpy(), want_s)
+    np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
+
+
 # ---- attention with MX-FP8 Q and K --------------------------------------------------------
 
 SCALE = 1.0 / math.sqrt(128)
