@@ -449,7 +449,7 @@ def dsattn_attn_fwd_reordered(rule, param, q, k, v, q_index, kv_index, o=None, s
     """``dsattn_attn_fwd_ex`` over queries taken in ``q_index`` order and keys/values in
     ``kv_index`` order (int32 GPU tensors); o and lse_out come back in the original query
     order, mask_out and stats_out describe the reordered tiles.  ``workspace`` (a uint8
-    GPU tensor) is allocated here when not given."""
+    GPU tensor) is allocated here, from the pool of the call's stream, when not given."""
     import torch
 
     o = _out(q, o)
@@ -461,7 +461,7 @@ def dsattn_attn_fwd_reordered(rule, param, q, k, v, q_index, kv_index, o=None, s
             raise ValueError(f"{name} must be a contiguous int32 GPU tensor of N={N} entries")
     need = dsattn_reordered_workspace_bytes(B, H, N, d, lse_out is not None)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
+        workspace = _workspace(max(need, 1), q.device, stream)
     a = DsAttnArgs(rule, param, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                    B, H, N, d, scale, tile_q, tile_k, _stream(stream), st, mk, ls, key_order)
     rc = lib().dsattn_attn_fwd_reordered(ctypes.byref(a), q_index.data_ptr(),

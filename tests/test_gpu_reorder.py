@@ -286,3 +286,40 @@ def test_reordered_wan720p_sampled():
         print(rep, f"full-run tile sparsity={float(g.mask.mean()):.4f}", flush=True)
         assert_parity(rep)
         assert np.array_equal(g.stats, expected_stats_from_mask(g.mask, w.N))
+
+
+@pytest.mark.parametrize("lse", [False, True])
+def test_side_stream_call_keeps_its_own_workspace(lse):
+    """A call on a side stream without a workspace: memory that the current stream allocates
+    and overwrites right after the call returns, with the side stream still busy ahead of the
+    call's kernels, is not the call's scratch."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"reordered on a side stream lse={lse}")
+    B, H, grid = 1, 2, (3, 21, 26)
+    q, k, v, _ = make_video_qkv(B, H, grid, 5.0, 5.0, True, 13)
+    N = q.shape[2]
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    qi, ki = dev_index(block_order(grid, (2, 8, 8))), dev_index(block_order(grid, (1, 8, 8)))
+    need = dsa.dsattn_reordered_workspace_bytes(B, H, N, 128, lse)
+
+    def call(o, ls, **more):
+        dsa.dsattn_attn_fwd_reordered(dsa.RULE_DYNSPARSE_LAMBDA, -6.0, qd, kd, vd, qi, ki, o,
+                                      scale=SCALE, lse_out=ls if lse else None, **more)
+
+    want, want_ls = torch.empty_like(qd), torch.zeros(B, H, N, device="cuda")
+    call(want, want_ls, workspace=torch.empty(need, dtype=torch.uint8, device="cuda"))
+    o, ls = torch.zeros_like(qd), torch.zeros(B, H, N, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)                 # some milliseconds
+        call(o, ls, stream=side)
+        grabbed = [torch.empty(need, dtype=torch.uint8, device="cuda").fill_(0x7f)
+                   for _ in range(4)]
+        torch.cuda.synchronize()
+        del grabbed
+        assert torch.equal(o.view(torch.int16), want.view(torch.int16))
+        assert torch.equal(ls, want_ls)
