@@ -206,17 +206,20 @@ def _stream(stream):
 
 def _workspace(nbytes, device, stream):
     """Scratch of one call, from the pool of the stream that the call runs on: once this
-    reference is gone, only later work of that stream can get the memory."""
+    reference is gone, only later work of that stream can get the memory.  (Without `stream`
+    that is the current stream of the current device, wherever the tensors are; `device` is
+    the tensors', for a stream that does not name its own.)"""
     import torch
 
     if nbytes == 0:
         return None
     if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     if not isinstance(stream, torch.cuda.Stream):
-        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+        stream = torch.cuda.ExternalStream(stream.cuda_stream,
+                                           device=getattr(stream, "device", device))
     with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return torch.empty(nbytes, dtype=torch.uint8, device=stream.device)
 
 
 def _out(q, o):
