@@ -15,6 +15,7 @@ B*H*N elements.
 
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -204,22 +205,35 @@ def _stream(stream):
         torch.cuda.current_device())
 
 
-def _workspace(nbytes, device, stream):
+def _workspace(nbytes, device, stream, optional=False):
     """Scratch of one call, from the pool of the stream that the call runs on: once this
     reference is gone, only later work of that stream can get the memory.  (Without `stream`
     that is the current stream of the current device, wherever the tensors are; `device` is
-    the tensors', for a stream that does not name its own.)"""
+    the tensors', for a stream that does not name its own.)
+
+    `optional`: the call gives the same result without, and gets None where memory is short,
+    and while the stream is captured: a graph outlives the call, and under a capture that torch
+    did not begin the memory would go back to other users between the replays."""
     import torch
 
     if nbytes == 0:
         return None
     if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-    if not isinstance(stream, torch.cuda.Stream):
-        stream = torch.cuda.ExternalStream(stream.cuda_stream,
-                                           device=getattr(stream, "device", device))
-    with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=stream.device)
+        on, device = contextlib.nullcontext(), "cuda"
+    else:
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream,
+                                               device=getattr(stream, "device", device))
+        on, device = torch.cuda.stream(stream), stream.device
+    with on:
+        if not optional:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            return None
 
 
 def _out(q, o):
@@ -434,7 +448,7 @@ def dsattn_key_mean(k, out=None, stream=None):
     B, H, N, d = (int(x) for x in k.shape)
     out = torch.empty((B, H, d), dtype=torch.float32, device=k.device) if out is None else out
     need = lib().dsattn_key_mean_workspace_bytes(B * H, N, d)
-    ws = _workspace(need, k.device, stream)
+    ws = _workspace(need, k.device, stream, optional=True)
     rc = lib().dsattn_key_mean_ws(k.data_ptr(), out.data_ptr(), B * H, N, d,
                                   None if ws is None else ws.data_ptr(), need, _stream(stream))
     _check(rc, "dsattn_key_mean")

@@ -120,6 +120,40 @@ def test_quantise_and_q8_attention_replays_match_eager():
             assert torch.equal(a, b), rep
 
 
+@pytest.mark.parametrize("side", [False, True])
+def test_captured_key_mean_of_many_keys_allocates_nothing(side):
+    """From 16384 keys on the eager call takes scratch; the captured one does without, with the
+    same bits, so that nothing of the graph lies in memory that others can get."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"graph: key mean of 20001 keys side={side}")
+    g0 = torch.Generator(device="cuda").manual_seed(3)
+    k = (torch.randn(1, 3, 20001, 128, device="cuda", generator=g0) + 0.5).to(torch.bfloat16)
+    mean = torch.zeros(1, 3, 128, device="cuda")
+    eager = dsa.dsattn_key_mean(k)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    other = torch.cuda.Stream()
+    with torch.cuda.graph(g):
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        if side:
+            other.wait_stream(torch.cuda.current_stream())
+        dsa.dsattn_key_mean(k, out=mean, stream=other if side else None)
+        if side:
+            torch.cuda.current_stream().wait_stream(other)
+        after = torch.cuda.memory_stats()["allocation.all.allocated"]
+    assert after == before
+    for rep in range(4):
+        if rep:
+            k.mul_(1.5 if rep % 2 else 0.75)
+            eager = dsa.dsattn_key_mean(k)
+        mean.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(mean, eager), rep
+
+
 def test_diagonal_rule_then_mask_reuse_replays_match_eager():
     """One graph holding a DynSparse call in diagonal-first order that writes its mask and
     a mask-reuse call that consumes it: every replay (new inputs each time) equals the
