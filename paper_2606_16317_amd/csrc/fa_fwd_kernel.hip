@@ -1839,15 +1839,6 @@ fa_fwd_mask_kernel(FwdParams p) {
   store_rows<GATHER>(p, o, rs, cx, head_off, bh, qrow);
 }
 
-__global__ void zero_u64_kernel(uint64_t* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-}  // namespace
-
-namespace {
-
 // The rule of a checked request as a template parameter; the dense rule keeps every tile, so
 // that the visit order changes nothing but the rounding of the sums: it always walks
 // ascending.
@@ -1920,27 +1911,50 @@ hipError_t launch_format(int rule, const FwdParams& params, dim3 grid, hipStream
     hipLaunchKernelGGL((fa_fwd_mask_kernel<UNIT, GATHER>), grid, dim3(kThreads), 0, stream, p);
     return hipGetLastError();
   }
-  if (p.qk_format == kQkMxfp8) {
-    if (p.q8 == nullptr || p.k8 == nullptr || p.q_scales == nullptr || p.k_scales == nullptr ||
-        GATHER)
-      return hipErrorInvalidValue;
-    return launch_order<UNIT, true, false>(rule, p, grid, stream);
+  if constexpr (!GATHER) {
+    if (p.qk_format == kQkMxfp8) {
+      if (p.q8 == nullptr || p.k8 == nullptr || p.q_scales == nullptr || p.k_scales == nullptr)
+        return hipErrorInvalidValue;
+      return launch_order<UNIT, true, false>(rule, p, grid, stream);
+    }
+  } else if (p.qk_format == kQkMxfp8) {
+    return hipErrorInvalidValue;
   }
   return launch_order<UNIT, false, GATHER>(rule, p, grid, stream);
 }
 
+template <bool GATHER>
+hipError_t launch_unit(int rule, int unit_rows, const FwdParams& p, int bh, hipStream_t stream) {
+  const dim3 grid((unsigned)p.n_qt, (unsigned)bh);
+  if (unit_rows == kTQ) return launch_format<kTQ, GATHER>(rule, p, grid, stream);
+  if (unit_rows == 32) return launch_format<32, GATHER>(rule, p, grid, stream);
+  return hipErrorInvalidValue;
+}
+
+#ifndef DSATTN_GATHER_KERNELS
+__global__ void zero_u64_kernel(uint64_t* __restrict__ p, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+#endif
+
 }  // namespace
 
+// fa_fwd_gather_kernel.hip compiles this file once more, for the kernels that read their
+// queries through p.q_row alone.  In one unit with them the compiler formed the K addresses of
+// every plain bf16 kernel differently (the inliner sees two callers of each helper): one more
+// register, two to six more operations in the prologue, and tiny calls 0.6 % slower.
+#ifdef DSATTN_GATHER_KERNELS
+hipError_t launch_fa_fwd_gather(int rule, int unit_rows, const FwdParams& p, int bh,
+                                hipStream_t stream) {
+  return launch_unit<true>(rule, unit_rows, p, bh, stream);
+}
+#else
 hipError_t launch_fa_fwd(int rule, int unit_rows, const FwdParams& p, int bh,
                          hipStream_t stream) {
-  const dim3 grid((unsigned)p.n_qt, (unsigned)bh);
-  if (unit_rows == kTQ)
-    return p.q_row != nullptr ? launch_format<kTQ, true>(rule, p, grid, stream)
-                              : launch_format<kTQ, false>(rule, p, grid, stream);
-  if (unit_rows == 32)
-    return p.q_row != nullptr ? launch_format<32, true>(rule, p, grid, stream)
-                              : launch_format<32, false>(rule, p, grid, stream);
-  return hipErrorInvalidValue;
+  return p.q_row != nullptr ? launch_fa_fwd_gather(rule, unit_rows, p, bh, stream)
+                            : launch_unit<false>(rule, unit_rows, p, bh, stream);
 }
 
 hipError_t launch_zero_u64(uint64_t* ptr, int n, hipStream_t stream) {
@@ -1950,5 +1964,6 @@ hipError_t launch_zero_u64(uint64_t* ptr, int n, hipStream_t stream) {
                      stream, ptr, n);
   return hipGetLastError();
 }
+#endif
 
 }  // namespace dsattn

@@ -46,6 +46,10 @@ struct FwdParams {
 hipError_t launch_fa_fwd(int rule, int unit_rows, const FwdParams& p, int bh,
                          hipStream_t stream);
 
+// launch_fa_fwd with a gather map (p.q_row not null), which it calls for one.
+hipError_t launch_fa_fwd_gather(int rule, int unit_rows, const FwdParams& p, int bh,
+                                hipStream_t stream);
+
 // Enqueue a fill of n uint64 zeros (a kernel rather than a memset node, so the call can be
 // captured into a graph and replayed).
 hipError_t launch_zero_u64(uint64_t* ptr, int n, hipStream_t stream);
