@@ -168,6 +168,57 @@ __global__ __launch_bounds__(kThreads) void quantize_mxfp8_kernel(
   }
 }
 
+// Several short groups a workgroup: blockIdx.x takes `groups` whole groups (groups *
+// group_chunks <= kThreads * kChunks), and a thread finds each chunk's group and column by
+// exact multiplications with rounded-up 2^32 / group_chunks and 2^32 / chunks_per_row (the
+// divisors are at least 4, they and the dividends below 2^11).
+//
+// Why: with a workgroup a group, a shift per row of 128 values (16 chunks) left 1008 of 1024
+// chunk places idle: 3024000 such rows 2418 us, now 468 (5.8 TB/s; 75600 rows 70.6, now 11.6;
+// one thread a block took 486 and 15.1).  Source and codes pass by the caches that a shift
+// vector's two halves are read through (without: 516).  At one group a workgroup (33 rows of
+// 128, 215 us, 267 before) quantize_mxfp8_kernel does as well, so the line lies at two.
+__global__ __launch_bounds__(kThreads) void quantize_mxfp8_short_kernel(
+    const u32x4* __restrict__ src, u32x2* __restrict__ codes, uint8_t* __restrict__ scales,
+    long long n_chunks, const float* __restrict__ shift, uint32_t chunks_per_row,
+    uint32_t group_chunks, uint32_t groups, uint32_t row_magic, uint32_t group_magic) {
+  const long long base_group = (long long)blockIdx.x * groups;
+  const long long base = base_group * group_chunks;
+  const uint32_t count =
+      (uint32_t)min((long long)(groups * group_chunks), n_chunks - base);
+  u32x4 w[kChunks];
+#pragma unroll
+  for (int u = 0; u < kChunks; ++u) {
+    const uint32_t at = threadIdx.x + u * kThreads;
+    w[u] = at < count ? __builtin_nontemporal_load(&src[base + at]) : u32x4{0, 0, 0, 0};
+  }
+  const float4* vectors = reinterpret_cast<const float4*>(shift) + 2 * base_group * chunks_per_row;
+  float4 s4[kChunks][2];
+#pragma unroll
+  for (int u = 0; u < kChunks; ++u) {
+    const uint32_t at = threadIdx.x + u * kThreads < count ? threadIdx.x + u * kThreads : 0;
+    const uint32_t group = __umulhi(at, group_magic);
+    const uint32_t rest = at - group * group_chunks;
+    const uint32_t col = rest - __umulhi(rest, row_magic) * chunks_per_row;
+    const uint32_t vec = 2 * (group * chunks_per_row + col);
+    s4[u][0] = vectors[vec];
+    s4[u][1] = vectors[vec + 1];
+  }
+#pragma unroll
+  for (int u = 0; u < kChunks; ++u) {
+    const uint32_t at = threadIdx.x + u * kThreads;
+    const float4 a = s4[u][0], b = s4[u][1];
+    const float sh[kChunkValues] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    u32x2 out;
+    uint32_t scode;
+    quantize_chunk<true>(w[u], sh, out, scode);
+    if (at < count) {
+      __builtin_nontemporal_store(out, &codes[base + at]);
+      if ((threadIdx.x & 3) == 0) scales[(base + at) >> 2] = (uint8_t)scode;
+    }
+  }
+}
+
 // Mean over the N keys of every head.  A workgroup takes one column group of a head:
 // kMeanCols columns (64 bytes of every row; all of a row when d is smaller).  Thread t
 // sums 16-byte chunk t % C of rows t / C, t / C + P, ... (C chunks per group, P =
@@ -316,6 +367,16 @@ hipError_t launch_quantize_mxfp8(const void* src, void* codes, void* scales,
   const bool one = shift == nullptr || group_rows >= rows;
   const long long group_chunks = one ? n_chunks : group_rows * cpr;
   const long long groups = (n_chunks + group_chunks - 1) / group_chunks;
+  if (!one && 2 * group_chunks <= kThreads * kChunks) {   // at least two groups a workgroup
+    const long long per = kThreads * kChunks / group_chunks;
+    const auto magic = [](long long x) { return (uint32_t)(((1ull << 32) + x - 1) / x); };
+    hipLaunchKernelGGL(quantize_mxfp8_short_kernel, dim3((unsigned)((groups + per - 1) / per)),
+                       dim3(kThreads), 0, stream, static_cast<const u32x4*>(src),
+                       static_cast<u32x2*>(codes), static_cast<uint8_t*>(scales), n_chunks, shift,
+                       (uint32_t)cpr, (uint32_t)group_chunks, (uint32_t)per, magic(cpr),
+                       magic(group_chunks));
+    return hipGetLastError();
+  }
   const long long runs = (group_chunks + kThreads * kChunks - 1) / (kThreads * kChunks);
   const dim3 grid((unsigned)runs, (unsigned)(groups < 65535 ? groups : 65535));
   if (shift == nullptr)

@@ -392,6 +392,34 @@ def test_shifted_quantize_row_lengths(H, N, d):
     np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
 
 
+@pytest.mark.parametrize("rows,group,d", [(2000, 1, 128), (2001, 2, 128), (777, 1, 32),
+                                          (1025, 3, 96), (500, 63, 128), (500, 64, 128),
+                                          (129, 5, 1056), (40, 1, 4096), (20, 1, 4128),
+                                          (20, 1, 8224), (3, 7, 128), (70000, 1, 32), (70, 17, 128)])
+def test_shifted_quantize_short_groups(rows, group, d):
+    """Shift groups of a few rows (a workgroup takes several groups of up to 512 chunks, 4096
+    values, and one longer one): any length, also one that does not divide the rows, and more
+    groups than a grid has in y."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"shifted quantize rows={rows} group={group} row_len={d}")
+    bits = make_random_qkv(1, 1, rows, d, 60 + group, k_std=2.0)[1]
+    kf = bf16_to_f64(bits)[0, 0]
+    shift = np.random.default_rng(rows).standard_normal((-(-rows // group), d))
+    shift = shift.astype(np.float32)
+    x, sh = to_device(bits), torch.from_numpy(shift).cuda()
+    codes = torch.full((rows, d), 0x7f, dtype=torch.uint8, device="cuda")
+    scales = torch.full((rows, d // 32), 0xff, dtype=torch.uint8, device="cuda")
+    assert dsa.lib().dsattn_quantize_mxfp8_shift(
+        x.data_ptr(), sh.data_ptr(), codes.data_ptr(), scales.data_ptr(), rows, d, group,
+        torch.cuda.current_stream().cuda_stream) == 0
+    y = kf.astype(np.float32) - np.repeat(shift, group, axis=0)[:rows]
+    want_c, want_s = quantize_mxfp8(y.astype(np.float64))
+    np.testing.assert_array_equal(scales.cpu().numpy(), want_s)
+    np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
+
+
 @pytest.mark.parametrize("H,N,d", [(1, 16384, 128), (2, 16385, 32), (3, 17407, 256),
                                    (2, 16384 + 1024 * 2 + 63, 64), (9, 20001, 128)])
 def test_key_mean_split_has_the_same_bits(H, N, d):
