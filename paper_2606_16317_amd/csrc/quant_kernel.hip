@@ -234,16 +234,22 @@ constexpr int kMeanCols = 32;
 constexpr int kMeanUnroll = 8;
 constexpr int kMeanPhases = kMeanThreads / (kMeanCols / 8);   // partial sums for d >= 32
 constexpr int kXcds = 8;       // accelerator dies; workgroups are dealt to them round-robin
+// Fewer heads than this leave most XCDs idle in that order; their column groups go to one XCD
+// each instead.  Measured as an XCD a head -> spread, us: 1 x 32760 x 128 39 -> 28, 1 x 16384 x
+// 256 22.5 -> 14.3, 3 x 8192 x 256 9.1 -> 8.3; 5 x 16384 x 128 the other way, 15.4 -> 21.6.
+constexpr int kMeanSpreadHeads = 4;
 
 __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __restrict__ k,
                                                                 float* __restrict__ mean,
-                                                                int bh, int N, int d) {
+                                                                int bh, int N, int d,
+                                                                bool spread) {
   __shared__ float part[kMeanThreads * 8];
   const int cols = d < kMeanCols ? d : kMeanCols;
-  const int groups = d / cols;
-  const int slot = (int)(blockIdx.x / kXcds);          // place in this XCD's order
-  const int head = (slot / groups) * kXcds + (int)(blockIdx.x % kXcds);
-  const int group = slot % groups;
+  const int log_groups = __builtin_ctz(d) - __builtin_ctz(cols);   // powers of two
+  const int slot = (int)(spread ? blockIdx.x : blockIdx.x / kXcds);   // place in the order
+  const int group = slot & ((1 << log_groups) - 1);
+  int head = slot >> log_groups;
+  if (!spread) head = head * kXcds + (int)(blockIdx.x % kXcds);
   if (head >= bh) return;
   const int cpg = cols >> 3;                 // 16-byte chunks per group and row
   const int cpr = d >> 3;                    // chunks per row
@@ -269,14 +275,15 @@ __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __r
 #pragma unroll
     for (int u = 0; u < kMeanUnroll; ++u) add(x[u]);
   }
-  for (; r + 3 * par < N; r += 4 * par) {
-    u32x4 x[4];
+  if (r < N) {   // the rest in one batch too; adding -0 changes no sum
+    u32x4 x[kMeanUnroll];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = base[(size_t)(r + u * par) * cpr];
+    for (int u = 0; u < kMeanUnroll; ++u)
+      x[u] = u * par < N - r ? base[(size_t)(r + u * par) * cpr]
+                             : u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
 #pragma unroll
-    for (int u = 0; u < 4; ++u) add(x[u]);
+    for (int u = 0; u < kMeanUnroll; ++u) add(x[u]);
   }
-  for (; r < N; r += par) add(base[(size_t)r * cpr]);
 #pragma unroll
   for (int i = 0; i < 8; ++i) part[t * 8 + i] = acc[i];
   __syncthreads();
@@ -409,9 +416,10 @@ hipError_t launch_key_mean(const void* k, float* mean, int bh, int N, int d, flo
     return hipGetLastError();
   }
   const int groups = d < kMeanCols ? 1 : d / kMeanCols;
-  const long long grid = (long long)((bh + kXcds - 1) / kXcds) * kXcds * groups;
+  const bool spread = bh < kMeanSpreadHeads;
+  const long long grid = (long long)(spread ? bh : (bh + kXcds - 1) / kXcds * kXcds) * groups;
   hipLaunchKernelGGL(key_mean_kernel, dim3((unsigned)grid), dim3(kMeanThreads), 0, stream,
-                     static_cast<const u32x4*>(k), mean, bh, N, d);
+                     static_cast<const u32x4*>(k), mean, bh, N, d, spread);
   return hipGetLastError();
 }
 

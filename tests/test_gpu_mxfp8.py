@@ -392,6 +392,73 @@ def test_shifted_quantize_row_lengths(H, N, d):
     np.testing.assert_array_equal(codes.cpu().numpy(), want_c)
 
 
+@pytest.mark.parametrize("H", [1, 3, 4, 9])
+@pytest.mark.parametrize("N,d", [(1, 128), (63, 128), (65, 32), (511, 128), (513, 256),
+                                 (777, 1024), (2049, 8), (2500, 16), (4100, 64)])
+def test_key_mean_bits_of_the_fixed_order(H, N, d):
+    """Below and above the head count from which a head's column groups share an XCD, with
+    whole batches of rows and remainders: the bits of the documented order in float32 (phase p
+    sums rows p, p + P, ...; the phases are added in order)."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce(f"key mean order H={H} N={N} d={d}")
+    par = 256 // (min(d, 32) // 8)
+    bits = make_random_qkv(1, H, N, d, N + H, k_std=2.0)[1]
+    x = bf16_to_f64(bits)[0].astype(np.float32)
+    steps = -(-N // par)
+    rows = np.full((H, steps * par, d), -0.0, np.float32)
+    rows[:, :N] = x
+    acc = np.zeros((H, par, d), np.float32)
+    for chunk in rows.reshape(H, steps, par, d).swapaxes(0, 1):
+        acc += chunk
+    total = np.zeros((H, d), np.float32)
+    for phase in range(par):
+        total += acc[:, phase]
+    want = total * (np.float32(1) / np.float32(N))
+    got = dsa.dsattn_key_mean(to_device(bits)).cpu().numpy()[0]
+    np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+def test_key_mean_workspace_refusals():
+    """A workspace too small, misaligned, on the host, or over the keys or the mean is refused
+    before anything runs; one of the exact size right behind the keys is taken."""
+    import torch
+    import paper_2606_16317_amd as dsa
+
+    announce("key mean workspace refusals")
+    L = dsa.lib()
+    H, N, d = 2, 16384, 128
+    need = L.dsattn_key_mean_workspace_bytes(H, N, d)
+    k_bytes, m_bytes = H * N * d * 2, H * d * 4
+    assert need == H * 64 * d * 4
+    buf = torch.zeros(k_bytes + need + m_bytes + 64, dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(9)
+    keys = torch.randn(1, H, N, d, device="cuda", generator=g).to(torch.bfloat16)
+    buf[:k_bytes] = keys.view(torch.uint8).reshape(-1)
+    base = buf.data_ptr()
+    assert base % 16 == 0
+    ws, m = base + k_bytes, base + k_bytes + need
+    host = torch.zeros(need, dtype=torch.uint8)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def call(w, size=need):
+        buf[k_bytes + need:] = 7
+        return L.dsattn_key_mean_ws(base, m, H, N, d, w, size, stream), dsa.last_error()
+
+    for w, size, word in [(ws, need - 1, "too small"), (ws, 0, "too small"),
+                          (ws + 4, need, "aligned"), (host.data_ptr(), need, "device pointer"),
+                          (base, need, "overlap"), (ws - 16, need, "overlap"),
+                          (m - need + 16, need, "overlap"), (m, need, "overlap")]:
+        rc, err = call(w, size)
+        torch.cuda.synchronize()
+        assert rc == -1 and word in err, (w - base, size, rc, err)
+        assert bool((buf[k_bytes + need:] == 7).all())
+    assert call(ws) == (0, "")
+    got = buf[k_bytes + need:k_bytes + need + m_bytes].view(torch.float32)
+    assert torch.equal(got, dsa.dsattn_key_mean(keys).reshape(-1))
+
+
 @pytest.mark.parametrize("rows,group,d", [(2000, 1, 128), (2001, 2, 128), (777, 1, 32),
                                           (1025, 3, 96), (500, 63, 128), (500, 64, 128),
                                           (129, 5, 1056), (40, 1, 4096), (20, 1, 4128),
