@@ -181,9 +181,10 @@ def test_wan720p_reuse_of_lambda_mask():
                                              (64 * 256, 32, 128), (64 * 257 - 63, 32, 64),
                                              (64 * 1025 - 1, 128, 128), (262144, 32, 64)])
 def test_visit_list_at_run_and_round_edges(N, tile_q, tile_k):
-    """Key-tile counts around a run of 64, a round of 256, four rounds and the longest list:
-    sampled rows against float64 attention over the kept keys (bf16 output and bf16
-    probabilities: 2^-8 each, four standard deviations over few keys stay below 2e-2)."""
+    """Key-tile counts around a run of 64, a round of 256, four rounds and the longest row of a
+    mask, with a few visited tiles each: sampled rows against float64 attention over the kept
+    keys (bf16 output and bf16 probabilities: 2^-8 each, four standard deviations over few keys
+    stay below 2e-2)."""
     import torch
 
     announce(f"mask list N={N} tile_q={tile_q} tile_k={tile_k}")
@@ -211,5 +212,46 @@ def test_visit_list_at_run_and_round_edges(N, tile_q, tile_k):
         s = (qf[r0:r1] @ kf[keys].t().contiguous()) * SCALE
         want = torch.softmax(s, 1) @ vf[keys]
         assert float((o.cuda() - want).abs().max()) < 2e-2
+        lse = torch.from_numpy(g.lse[0, 0, r0:r1].astype(np.float64)).cuda()
+        assert float((lse - torch.logsumexp(s, 1)).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("N,tile_q,tile_k", [(262144, 32, 64), (262144, 128, 64),
+                                             (64 * 1025 - 1, 32, 64)])
+def test_full_visit_lists(N, tile_q, tile_k):
+    """Query tiles that visit all key tiles (4096 at most) or most of them, among tiles that
+    visit none: full runs of 64, every offset inside one, and the last list entries.  Sampled
+    rows against float64 attention over the kept keys.  With many keys the output is small
+    against its rounding: relative 2-norm below 1e-2 (bf16 probabilities and output, 2^-9 each,
+    and float32 sums)."""
+    import torch
+
+    announce(f"full mask lists N={N} tile_q={tile_q}")
+    rng = np.random.default_rng(N + tile_q)
+    q, k, v = make_random_qkv(1, 1, N, 128, 78, q_std=1.0, k_std=1.0)
+    n_qu, n_kd = -(-N // tile_q), -(-N // tile_k)
+    mask = np.ones((1, 1, n_qu, n_kd), np.uint8)
+    full, most, last = 0, 128 // tile_q, n_qu - 1       # three workgroups
+    mask[0, 0, full] = 0
+    mask[0, 0, most] = rng.random(n_kd) < 0.1
+    mask[0, 0, last] = rng.random(n_kd) < 0.02
+    if tile_q == 32:                                    # units that keep other tiles than those
+        mask[0, 0, most + 1] = 1 - mask[0, 0, most]
+        mask[0, 0, full + 3, 1::2] = 0
+    qd, kd, vd = upload(q, k, v)
+    g = run_reuse(qd, kd, vd, mask, tile_q, tile_k)
+    np.testing.assert_array_equal(g.mask.reshape(mask.shape), mask)
+    assert (g.stats == expected_stats_from_mask(mask, N, tile_q, tile_k)).all()
+    qf, kf, vf = (x[0, 0].double() for x in (qd, kd, vd))
+    for u in sorted({full, full + 3, most, most + 1, last, n_qu // 2}):
+        r0, r1 = u * tile_q, min(N, (u + 1) * tile_q)
+        o = torch.from_numpy(oracle.bf16_to_f64(g.o[0, 0, r0:r1])).cuda()
+        keys = torch.from_numpy(np.repeat(mask[0, 0, u] == 0, tile_k)[:N]).cuda()
+        if not bool(keys.any()):
+            assert bool((o == 0).all()) and np.isneginf(g.lse[0, 0, r0:r1]).all()
+            continue
+        s = (qf[r0:r1] @ kf[keys].t().contiguous()) * SCALE
+        want = torch.softmax(s, 1) @ vf[keys]
+        assert float((o - want).norm() / want.norm()) < 1e-2, u
         lse = torch.from_numpy(g.lse[0, 0, r0:r1].astype(np.float64)).cuda()
         assert float((lse - torch.logsumexp(s, 1)).abs().max()) < 1e-4

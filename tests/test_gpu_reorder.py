@@ -196,13 +196,24 @@ def test_reordered_call_equals_gathers_plain_call_and_scatters(rule, param, tile
     """Queries read and outputs written in place through q_index have the bits of moving
     q, k and v first, the plain call, and moving o and the LSE back; entries outside the
     sequence stand for a zero query and leave their output rows alone."""
+    check_in_place(rule, param, tile_q, tile_k, order, N, 2, 2)
+
+
+@pytest.mark.parametrize("tile_q,tile_k", [(32, 64), (128, 128)])
+@pytest.mark.parametrize("B,H,N", [(3, 43, 600), (1, 15, 36 * 128 - 5), (1, 2, 257 * 128 + 1)])
+def test_reordered_mask_reuse_with_interleaved_heads(B, H, N, tile_q, tile_k):
+    """The same above 512 workgroups, where a reused mask's launch interleaves its heads: the
+    gather map belongs to the tile, not to the place in the grid."""
+    check_in_place("mask", 0.0, tile_q, tile_k, 0, N, B, H)
+
+
+def check_in_place(rule, param, tile_q, tile_k, order, N, B, H):
     import ctypes
 
     import torch
     import paper_2606_16317_amd as dsa
 
-    announce(f"reordered in place {rule}={param} tile_q={tile_q} tile_k={tile_k} N={N}")
-    B, H = 2, 2
+    announce(f"reordered in place {rule}={param} {tile_q}x{tile_k} B={B} H={H} N={N}")
     qd, kd, vd = (to_device(x) for x in make_random_qkv(B, H, N, 128, N, q_std=2.0, k_std=2.0))
     rng = np.random.default_rng(N)
     qi, ki = rng.permutation(N), rng.permutation(N)
