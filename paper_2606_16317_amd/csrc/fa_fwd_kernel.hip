@@ -1380,12 +1380,6 @@ __device__ __forceinline__ void half_tile_step(int j, const f32x16 (&s_cur)[2],
   }
 }
 
-// UNIT: query rows per skip decision, 128 (the workgroup's tile) or 32 (one wave).
-// ORDER: key-tile visit order (ascending or diagonal-first).
-// Q8: Q and K in MX-FP8 (codes p.q8 / p.k8, exponents p.q_scales / p.k_scales), S = Q K^T
-// on the scaled fp8 MFMA; everything after S is the same as with bf16 Q and K.
-// BC: keys per skip decision: 64 (one tile), 128 (two tiles) or 32 (half a tile); 32
-// walks keys in ascending order only.
 // Head and query tile of this workgroup, from its place (bh, qt) in the grid: the heads are
 // taken eight at a time (what is left over four, two and one at a time) and the g heads of a
 // group interleaved, so that neighbours in dispatch order, which go to different XCDs, hold
@@ -1395,12 +1389,14 @@ __device__ __forceinline__ void half_tile_step(int j, const f32x16 (&s_cur)[2],
 // grid: a tile's g places hold the g heads, rotated.
 //
 // What bounds such launches: workgroups that skip at different rates, or walk different lists
-// of tiles, drift apart in the key loop, and their K and V then come from behind L2.  With two
-// or more heads in flight each XCD streamed all of them.  Measured as grid order -> this, us:
-// mask reuse 480p (N = 32760), 10 heads, 32-row units, 25 % kept 1657 -> 1586; 40 heads,
-// 128-row units 5160 -> 5047; N = 75600, 5 heads 3524 -> 3411; MX-FP8 480p, 10 heads,
-// lambda -8 3798 -> 3616.  Groups of 8 without the rotation gain as much on even heads and
-// lose up to 6 % where heads skip differently.  Where the line lies: interleaves_heads().
+// of tiles, drift apart in the key loop, and their K and V then come from behind L2.  L2
+// requests and misses, grid order -> this, at N = 32760 and 10 heads: mask reuse, 32-row units,
+// 25 % kept, 118 million with 81 -> 64 million missed; MX-FP8 at lambda -8, 244 with 44 -> 10.
+// Times, us: mask reuse, 10 heads, 32-row units 1657 -> 1586; 40 heads, 128-row units 5160 ->
+// 5047; N = 75600, 5 heads 3524 -> 3411; MX-FP8, 24 heads at lambda -8 9238 -> 8930.  Groups of
+// 8 without the rotation gain as much on even heads and lose up to 6 % where heads skip
+// differently; runs of consecutive tiles without interleaving (each XCD an eighth of every
+// head) lost up to 8 % of mask reuse.  Where the line lies: interleaves_heads().
 __device__ __forceinline__ void interleave_heads(int n_qt, int& bh, int& qt) {
   const int heads = (int)gridDim.y;
   int base = 0, log_g = 3;
@@ -1416,6 +1412,12 @@ __device__ __forceinline__ void interleave_heads(int n_qt, int& bh, int& qt) {
   bh = base + ((place + qt / ((n_qt + g - 1) >> log_g)) & (g - 1));
 }
 
+// UNIT: query rows per skip decision, 128 (the workgroup's tile) or 32 (one wave).
+// ORDER: key-tile visit order (ascending or diagonal-first).
+// Q8: Q and K in MX-FP8 (codes p.q8 / p.k8, exponents p.q_scales / p.k_scales), S = Q K^T
+// on the scaled fp8 MFMA; everything after S is the same as with bf16 Q and K.
+// BC: keys per skip decision: 64 (one tile), 128 (two tiles) or 32 (half a tile); 32
+// walks keys in ascending order only.
 template <int RULE, int UNIT, int ORDER, bool Q8, int BC, bool GATHER>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2))) void
@@ -1634,10 +1636,10 @@ __device__ __forceinline__ void mask_tile_step(int j, int n_keep, const f32x16 (
   // With 32-row units a visited tile is one that some of the workgroup's units keep.  A wave
   // whose unit skips this one computes only the scores of the next, and nothing at all if it
   // skips that one too: the co-resident workgroup gets the cycles.  (480p, 10 heads, 25 % of
-  // the unit tiles kept, 33 % visited: 1839 us with every wave running every visited tile
-  // in full, 1765 this way; 720p, 40 heads 34.5 and 33.7 ms.  A launch that leaves the chip
-// idle, 2 heads of N = 4092 with 40 % kept: 53.4 us while the exponentials sank behind the
-// branch on keep_own, 49.9 with them pinned under the Q K^T MFMAs.)
+  // the unit tiles kept, 33 % visited, heads in grid order: 1839 us with every wave running
+  // every visited tile in full, 1765 this way; 720p, 40 heads 34.5 and 33.7 ms.  A launch that
+  // leaves the chip idle, 2 heads of N = 4092 with 40 % kept: 53.4 us while the exponentials
+  // sank behind the branch on keep_own, 49.9 with them pinned under the Q K^T MFMAs.)
   float rmax_kept = 0.f;
   if constexpr (UNIT == kTQ) {
     kept_tile(rs, o, s_cur, mhat, cx.c, s_next, sm.t.k[nb], sm.t.v[j & 1], qf, cx.r, cx.g,
@@ -1885,21 +1887,35 @@ hipError_t launch_order(int rule, const FwdParams& p, dim3 grid, hipStream_t str
 }
 
 // Whether a launch interleaves its heads (see interleave_heads).  Up to kResident workgroups
-// are all in flight at once, and there the order gained nothing (mask reuse, 3 heads of 122
-// query tiles: 220.0 us against 221.9).  Mask reuse gained 2 to 4 % at every size above that.
-// MX-FP8 rules gained 0 to 8 % with the threshold at or below lambda = -7.5 or tau = 0.01
-// (480p, 40 heads, lambda -8: 15.21 -> 14.60 ms; N = 75600, 10 heads: 18.95 -> 18.92; at worst
-// 0.6 % lost); with higher thresholds, where most tiles are skipped, heads differ more and 40
-// heads of 480p lost 0.5 % (lambda -7) and 2 % (-6).  The bf16 rules, whose key loop takes
-// longer, moved by -2 to +3 % at lambda -6 to -9 with no clear gain: grid order.
+// are all in flight at once: grid order.  Gains below are of interleaved against grid order,
+// over inputs of the video kind.
+//
+// Mask reuse: even head counts gain 1 to 9 % (means over 15 to 60 % kept and both units: 10 x
+// 7800 tokens +2, 8 x 10920 +4, 12 x 21840 +4, 8 x 32760 +5, 2 x 75600 +7; 16 x 7800 -0.4).
+// An odd count leaves one head in grid order behind the groups: 9 x 7800 -3, 9 x 15600 0, 3 x
+// 32760 -1, 7 x 32760 -1, but from 320 query tiles on 5 x 50400 +2, 3 x 75600 +4.
+//
+// MX-FP8 rules: interleaved workgroups stay in step, so that a launch takes whole rounds of
+// kResident.  With the last round at least 0.8 full, 8 to 40 heads of 32760 tokens at lambda =
+// -8 gained 1 to 4 %, 16 x 32000 2 %, 9 x 21504 1 %, other sizes nothing (7800 to 26000 tokens
+// within 1 %; at worst 13 x 30000, -2).  With little in it they lost what drifting apart hides
+// (8 x 33000, 4.03 rounds, -4 %; 12 x 21840, 4.01, -2; 3 x 32760, 1.5, -7 at recall 0.95), and
+// above 256 query tiles 8 x 36864 lost 3 % and 75600 was even.  With higher thresholds, where
+// most tiles are skipped, heads differ more: 10 x 32760 lost 4 % at lambda = -6 and, in three
+// runs, -2 to +1 at -7.  Dense: even everywhere.
+//
+// The bf16 rules, whose key loop takes longer, moved by -2 to +3 % with no clear gain.
 constexpr long long kResident = 512;          // workgroups in flight: two on each of 256 CUs
 bool interleaves_heads(int rule, const FwdParams& p, dim3 grid) {
-  if (grid.y < 2 || (long long)grid.x * grid.y <= kResident) return false;
-  if (rule == kRuleMask) return true;
-  if (p.qk_format != kQkMxfp8) return false;
+  const long long groups = (long long)grid.x * grid.y;
+  if (grid.y < 2 || groups <= kResident) return false;
+  if (rule == kRuleMask) return grid.y % 2 == 0 || grid.x > 320;
+  if (p.qk_format != kQkMxfp8 || grid.x > 256) return false;
+  const long long last = (groups - 1) % kResident + 1;   // workgroups of the last round
+  if (10 * last < 8 * kResident) return false;
   if (rule == kRuleDynSparse) return p.thr <= -10.82f;   // lambda <= -7.5, in log2 units
   if (rule == kRuleBlasst) return p.thr <= -6.64f;       // tau <= 0.01
-  return true;                                           // dense
+  return false;                                          // dense
 }
 
 template <int UNIT, bool GATHER>

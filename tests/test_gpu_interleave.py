@@ -1,4 +1,4 @@
-"""Launches that interleave their heads (mask reuse and MX-FP8 above 512 workgroups) against
+"""Launches that interleave their heads (of mask reuse and MX-FP8, above 512 workgroups) against
 the same heads called a few at a time, which run in grid order: workgroups do not depend on
 each other, so every output is the same bit for bit, whatever the order."""
 
@@ -9,6 +9,13 @@ pytestmark = pytest.mark.gpu
 # (heads, tokens): groups of 8, 4, 2 and 1 with ragged last tiles; one query tile a head;
 # a leftover single head; tile counts that the group size does not divide.
 SHAPES = [(15, 36 * 128 - 5), (43, 13 * 128 - 100), (130, 4 * 128), (520, 100), (2, 257 * 128 + 1)]
+# A reused mask's launch leaves an odd head count in grid order up to 320 query tiles: groups of
+# 8, 4 and 2, and leftover single heads above that.
+MASK_SHAPES = SHAPES + [(14, 37 * 128 - 5), (3, 321 * 128 - 70), (5, 320 * 128 + 1)]
+# An MX-FP8 launch interleaves if its last round of 512 workgroups is at least 0.8 full: the
+# same groups at such counts (the least full of them 410, one below 409).
+MXFP8_SHAPES = SHAPES + [(15, 64 * 128 - 5), (43, 23 * 128 - 100), (130, 7 * 128), (922, 100),
+                         (921, 100), (5, 193 * 128 + 1), (4, 256 * 128)]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -42,7 +49,7 @@ def check(torch, call, heads, n, tile_q, tile_k):
             assert torch.equal(x, whole[name][:, part]), name
 
 
-@pytest.mark.parametrize("heads,n", SHAPES)
+@pytest.mark.parametrize("heads,n", MASK_SHAPES)
 @pytest.mark.parametrize("tile_q,tile_k", [(128, 64), (32, 128), (32, 64)])
 def test_mask_reuse(gpu, heads, n, tile_q, tile_k):
     import paper_2606_16317_amd as dsa
@@ -63,7 +70,7 @@ def test_mask_reuse(gpu, heads, n, tile_q, tile_k):
     check(torch, call, heads, n, tile_q, tile_k)
 
 
-@pytest.mark.parametrize("heads,n", SHAPES)
+@pytest.mark.parametrize("heads,n", MXFP8_SHAPES)
 @pytest.mark.parametrize("rule,param,tile_q,tile_k", [
     ("RULE_DYNSPARSE_LAMBDA", -7.5, 128, 64), ("RULE_DYNSPARSE_LAMBDA", -8.0, 32, 32),
     ("RULE_BLASST", 1e-2, 128, 128), ("RULE_DENSE", 0.0, 128, 64)])
