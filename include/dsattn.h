@@ -292,12 +292,6 @@ int dsattn_quantize_mxfp8(const void* src, void* codes, void* scales, long long 
  * bf16 keys of d values (d a power of two in [8, 1024]; k 16-byte aligned, mean_out 4-byte
  * aligned, both device pointers).  The summation order is fixed, so repeated calls give
  * the same bits.  N must be > 0 when BH > 0.
- *
- * dsattn_quantize_mxfp8_shift: as dsattn_quantize_mxfp8 on the float32 values
- * x - shift[i / group_rows][c] (each difference rounded to nearest float32) for element c
- * of row i; shift is a 16-byte aligned device array of float32 [ceil(rows/group_rows)]
- * [row_len].  For keys [B][H][N][d] and the mean of dsattn_key_mean, group_rows = N.
- * x - shift must stay finite.
  */
 int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStream_t stream);
 
@@ -311,6 +305,13 @@ int dsattn_key_mean(const void* k, float* mean_out, int BH, int N, int d, hipStr
 size_t dsattn_key_mean_workspace_bytes(int BH, int N, int d);
 int dsattn_key_mean_ws(const void* k, float* mean_out, int BH, int N, int d, void* workspace,
                        size_t workspace_bytes, hipStream_t stream);
+
+/*
+ * dsattn_quantize_mxfp8 on the float32 values x - shift[i / group_rows][c] (each difference
+ * rounded to nearest float32) for element c of row i; shift is a 16-byte aligned device
+ * array of float32 [ceil(rows/group_rows)][row_len].  For keys [B][H][N][d] and the mean of
+ * dsattn_key_mean, group_rows = N.  x - shift must stay finite.
+ */
 int dsattn_quantize_mxfp8_shift(const void* src, const float* shift, void* codes, void* scales,
                                 long long rows, int row_len, long long group_rows,
                                 hipStream_t stream);

@@ -1,7 +1,8 @@
 """HIP graph capture of the C-ABI calls (torch.cuda.CUDAGraph over the library's kernels).
 
 The library clears stats_out with a fill kernel rather than a memset node, and allocates
-nothing, so a call can be captured and replayed.  Each graph is replayed several times
+nothing, so a call can be captured and replayed; the binding takes the key mean of many keys
+without its scratch while a stream is captured.  Each graph is replayed several times
 with the program's own eager work and synchronisations in between and with new inputs
 copied into the captured buffers; every replay must equal an eager call on the same
 inputs bit for bit (the kernels are deterministic).
