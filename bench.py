@@ -731,7 +731,7 @@ def counter_summary(dirs, command):
     vals = {}
     for d in dirs:
         for r in csv.DictReader(open(_find_csv(d, "counter_collection.csv"))):
-            m = re.search(r"fa_fwd_kernel<(\d), 128, 0, false, 64>", r["Kernel_Name"])
+            m = re.search(r"fa_fwd_kernel<(\d), 128, 0, false, 64(?:, false)?>", r["Kernel_Name"])
             if not m:
                 continue
             kern = KERNEL_RULES[m.group(1)]
@@ -778,8 +778,8 @@ def traffic_summary(fetch_dir, write_dir, workload, command):
             if r["Counter_Name"] != counter:
                 continue
             kib = float(r["Counter_Value"])
-            # DynSparse rule, 128-row units, ascending order, bf16 Q and K
-            if re.search(r"fa_fwd_kernel<2, 128, 0, false(, 64)?>", r["Kernel_Name"]):
+            # DynSparse rule, 128-row units, ascending order, bf16 Q and K in place
+            if re.search(r"fa_fwd_kernel<2, 128, 0, false(, 64(, false)?)?>", r["Kernel_Name"]):
                 vals["main"].append(kib)
             elif "AUnaryFunctor" in r["Kernel_Name"] or "MulFunctor" in r["Kernel_Name"]:
                 vals["copy"].append(kib)

@@ -83,6 +83,28 @@ def test_counter_summary_ratios(tmp_path):
     assert any("SQ_INSTS_VALU " in l and "per MFMA 5.600" in l for l in lines)
 
 
+def test_summaries_know_the_kernels_that_are_built(tmp_path):
+    """The names that the summaries look for have a value for each of the kernel's template
+    parameters; queries through an index (the last one true) are another kernel."""
+    import re
+
+    src = os.path.join(ROOT, "paper_2606_16317_amd", "csrc", "fa_fwd_kernel.hip")
+    params = re.search(r"template <([^>]*)>\s*__global__[^{;]*\bfa_fwd_kernel\(",
+                       open(src).read()).group(1)
+    names = [x.split()[-1] for x in params.split(",")]
+    assert names == ["RULE", "UNIT", "ORDER", "Q8", "BC", "GATHER"]
+    plain = "void dsattn::(anonymous namespace)::fa_fwd_kernel<2, 128, 0, false, 64, false>(X)"
+    gather = plain.replace("64, false", "64, true")
+    for d, counter in (("f", "FETCH_SIZE"), ("w", "WRITE_SIZE")):
+        _counters(str(tmp_path / d), [[1, COPY, counter, float(1 << 20)], [2, plain, counter, 50.0],
+                                      [3, gather, counter, 9.0e9]])
+    rec = bench.traffic_summary(str(tmp_path / "f"), str(tmp_path / "w"), "wl", "cmd")
+    assert rec["dispatches"] == [1, 1]
+    assert rec["bytes_per_launch"] == pytest.approx(2 * 50.0 * 1024)
+    text = bench.counter_summary([str(tmp_path / "f")], "cmd")
+    assert "fa_fwd_kernel<dynsparse>  dispatches per pass" in text and "50" in text
+
+
 def test_traffic_summary_scales_by_the_copy(tmp_path, monkeypatch):
     gib_kib = float(1 << 20)
     # the copy moves 1 GiB: FETCH_SIZE reads half of it, WRITE_SIZE all of it
