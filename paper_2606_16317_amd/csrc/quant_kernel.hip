@@ -310,9 +310,11 @@ __global__ __launch_bounds__(kMeanThreads) void key_mean_kernel(const u32x4* __r
 //
 // Why: a workgroup of key_mean_kernel reads at about 25 GB/s however many loads it has in
 // flight (line fills of its CU: each 64-byte piece brings in a whole line), and a head has
-// only four.  40 heads of 75600 keys: 196 us against 129 (6.0 TB/s); 5 heads of 32760:
-// 41 against 25.  At 2 x 8192 keys the second launch costs more than it saves (9 against
-// 13 us), so the split starts at kMeanSplitRows keys.
+// only four.  40 heads of 75600 keys: 196 us against 126 (6.1 TB/s); 5 heads of 32760: 40
+// against 24.  The second launch is paid back from about 8192 keys on with few heads (1 to 8:
+// 8.2 against 7.3 us) and later with many (40 x 12000: 20.6 against 23.2; 40 x 16384: 26.7 both;
+// 64 x 16384 39.4 against 41.6, the worst above the line).  kMeanSplitRows is where most head
+// counts gain by a quarter or more.
 constexpr int kMeanSplitUnroll = 16;
 constexpr int kMeanSplitRows = 16384;
 
