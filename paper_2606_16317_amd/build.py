@@ -28,7 +28,7 @@ LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 SAN_LIB_PATH = os.path.join(PKG_DIR, "libdsattn_san.so")
 ARCH = "gfx950"
 
-SOURCES = ["fa_fwd_kernel.hip", "fa_fwd_gather_kernel.hip", "reorder_kernel.hip",
+SOURCES = ["fa_fwd_kernel.hip", "fa_fwd_side_kernels.hip", "reorder_kernel.hip",
            "quant_kernel.hip", "dsattn_api.cpp"]
 
 

@@ -493,6 +493,7 @@ __device__ __forceinline__ void kept_tile(RowState& rs, f32x16 (&o)[4], const f3
 // exp2(-inf) = 0 and the P V phase left out.  (Branching around the P V phase alone keeps
 // one copy of the Q K^T phase; with two whole tile bodies under the branch the kernel
 // spills 90 to 300 registers and takes three times as long.)
+[[maybe_unused]]
 __device__ __forceinline__ void unit_tile(RowState& rs, f32x16 (&o)[4], const f32x16 (&s_cur)[2],
                                           float m_hat, float c, f32x16 (&s_next)[2],
                                           const uint16_t* kt, const uint16_t* vt,
@@ -1610,6 +1611,7 @@ fa_fwd_kernel(FwdParams p) {
 // decisions keeps or skips both 64-key tiles of each decision.
 
 // Visited tiles of one workgroup, ascending: (key tile << 4) | keep bit of each wave.
+[[maybe_unused]]
 __device__ __forceinline__ int list_tile(const MaskSmem& sm, int s) {
   return (int)__builtin_amdgcn_readfirstlane((uint32_t)sm.list[s] >> 4);
 }
@@ -1893,42 +1895,44 @@ hipError_t launch_order(int rule, const FwdParams& p, dim3 grid, hipStream_t str
 // over inputs of the video kind.
 //
 // Mask reuse: even head counts gain 1 to 9 % (means over 15 to 60 % kept and both units: 10 x
-// 7800 tokens +2, 8 x 10920 +4, 12 x 21840 +4, 8 x 32760 +5, 2 x 75600 +7; 16 x 7800 -0.4).
+// 7800 tokens +2, 8 x 10920 +4, 12 x 21840 +4, 8 x 32760 +5, 2 x 75600 +7; 14 x 7800 -1.5).
 // An odd count leaves one head in grid order behind the groups: 9 x 7800 -3, 9 x 15600 0, 3 x
-// 32760 -1, 7 x 32760 -1, but from 320 query tiles on 5 x 50400 +2, 3 x 75600 +4.
+// 32760 -1, 7 x 32760 -1, but from 320 query tiles on 5 x 50400 +2, 3 x 75600 +4.  With counters
+// asked for, odd counts gain too (17 x 4095 +12, 9 x 15600 +2, 5 x 32760 +4; 9 x 7800 -3): in grid
+// order the workgroups that end together all add to one head's four counters.
 //
 // MX-FP8 rules: interleaved workgroups stay in step, so that a launch takes whole rounds of
 // kResident.  With the last round at least 0.8 full, 8 to 40 heads of 32760 tokens at lambda =
 // -8 gained 1 to 4 %, 16 x 32000 2 %, 9 x 21504 1 %, other sizes nothing (7800 to 26000 tokens
 // within 1 %; at worst 13 x 30000, -2).  With little in it they lost what drifting apart hides
 // (8 x 33000, 4.03 rounds, -4 %; 12 x 21840, 4.01, -2; 3 x 32760, 1.5, -7 at recall 0.95), and
-// above 256 query tiles 8 x 36864 lost 3 % and 75600 was even.  With higher thresholds, where
-// most tiles are skipped, heads differ more: 10 x 32760 lost 4 % at lambda = -6 and, in three
-// runs, -2 to +1 at -7.  Dense: even everywhere.
+// above 256 query tiles 8 x 36864 lost 3 % and 75600 was even.  Up to 64 query tiles, where all
+// heads are in flight on every XCD either way, some launches of one to two and a half rounds
+// gain (12 and 24 x 6160 +5 and +4, 10 x 7800 +7) and the others are even (24 x 4095 -1).  With
+// higher thresholds, where most tiles are skipped, heads differ more: 10 x 32760 lost 4 % at
+// lambda = -6 and, in three runs, -2 to +1 at -7; 4 x 21840 lost 11 % at -6.
+// Dense: even, and with counters 2 to 15 % gained up to 16000 tokens (16 x 7800, 32-row units,
+// +15; 32760 tokens 0 to +3).
 //
 // The bf16 rules, whose key loop takes longer, moved by -2 to +3 % with no clear gain.
 constexpr long long kResident = 512;          // workgroups in flight: two on each of 256 CUs
 bool interleaves_heads(int rule, const FwdParams& p, dim3 grid) {
   const long long groups = (long long)grid.x * grid.y;
   if (grid.y < 2 || groups <= kResident) return false;
-  if (rule == kRuleMask) return grid.y % 2 == 0 || grid.x > 320;
-  if (p.qk_format != kQkMxfp8 || grid.x > 256) return false;
+  if (rule == kRuleMask) return p.stats != nullptr || grid.y % 2 == 0 || grid.x > 320;
+  if (p.qk_format != kQkMxfp8) return false;
+  if (rule == kRuleDense) return true;
   const long long last = (groups - 1) % kResident + 1;   // workgroups of the last round
-  if (10 * last < 8 * kResident) return false;
+  if (grid.x > 64 && (grid.x > 256 || 10 * last < 8 * kResident)) return false;
   if (rule == kRuleDynSparse) return p.thr <= -10.82f;   // lambda <= -7.5, in log2 units
-  if (rule == kRuleBlasst) return p.thr <= -6.64f;       // tau <= 0.01
-  return false;                                          // dense
+  return rule == kRuleBlasst && p.thr <= -6.64f;         // tau <= 0.01
 }
 
 template <int UNIT, bool GATHER>
 hipError_t launch_format(int rule, const FwdParams& params, dim3 grid, hipStream_t stream) {
   FwdParams p = params;
   p.interleave = interleaves_heads(rule, p, grid);
-  if (rule == kRuleMask) {
-    if (p.n_kt > kMaxMaskTiles || p.mask_in == nullptr) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fa_fwd_mask_kernel<UNIT, GATHER>), grid, dim3(kThreads), 0, stream, p);
-    return hipGetLastError();
-  }
+  if (rule == kRuleMask) return launch_fa_fwd_mask(UNIT, p, grid, stream);
   if constexpr (!GATHER) {
     if (p.qk_format == kQkMxfp8) {
       if (p.q8 == nullptr || p.k8 == nullptr || p.q_scales == nullptr || p.k_scales == nullptr)
@@ -1949,24 +1953,38 @@ hipError_t launch_unit(int rule, int unit_rows, const FwdParams& p, int bh, hipS
   return hipErrorInvalidValue;
 }
 
-#ifndef DSATTN_GATHER_KERNELS
+#ifndef DSATTN_SIDE_KERNELS
 __global__ void zero_u64_kernel(uint64_t* __restrict__ p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
-
 #endif
 
 }  // namespace
 
-// fa_fwd_gather_kernel.hip compiles this file once more, for the kernels that read their
-// queries through p.q_row alone.  In one unit with them the compiler formed the K addresses of
-// every plain bf16 kernel differently (the inliner sees two callers of each helper): one more
-// register, two to six more operations in the prologue, and tiny calls 0.6 % slower.
-#ifdef DSATTN_GATHER_KERNELS
+// fa_fwd_side_kernels.hip compiles this file once more, for mask reuse and for the kernels that
+// read their queries through p.q_row alone.  In one unit with the latter the compiler formed the
+// K addresses of every plain bf16 kernel differently (the inliner sees more callers of each
+// helper): one more register, two to six more operations in the prologue, and tiny calls 0.6 %
+// slower.  With the mask kernels here instead theirs changed (480p, 10 heads 0.6 % slower).
+#ifdef DSATTN_SIDE_KERNELS
 hipError_t launch_fa_fwd_gather(int rule, int unit_rows, const FwdParams& p, int bh,
                                 hipStream_t stream) {
   return launch_unit<true>(rule, unit_rows, p, bh, stream);
+}
+
+hipError_t launch_fa_fwd_mask(int unit_rows, const FwdParams& p, dim3 grid, hipStream_t stream) {
+  if (p.n_kt > kMaxMaskTiles || p.mask_in == nullptr) return hipErrorInvalidValue;
+  const dim3 block(kThreads);
+  if (unit_rows == kTQ && p.q_row == nullptr)
+    hipLaunchKernelGGL((fa_fwd_mask_kernel<kTQ, false>), grid, block, 0, stream, p);
+  else if (unit_rows == kTQ)
+    hipLaunchKernelGGL((fa_fwd_mask_kernel<kTQ, true>), grid, block, 0, stream, p);
+  else if (p.q_row == nullptr)
+    hipLaunchKernelGGL((fa_fwd_mask_kernel<32, false>), grid, block, 0, stream, p);
+  else
+    hipLaunchKernelGGL((fa_fwd_mask_kernel<32, true>), grid, block, 0, stream, p);
+  return hipGetLastError();
 }
 #else
 hipError_t launch_fa_fwd(int rule, int unit_rows, const FwdParams& p, int bh,

@@ -46,9 +46,11 @@ struct FwdParams {
 hipError_t launch_fa_fwd(int rule, int unit_rows, const FwdParams& p, int bh,
                          hipStream_t stream);
 
-// launch_fa_fwd with a gather map (p.q_row not null), which it calls for one.
+// Parts of launch_fa_fwd: a call with a gather map (p.q_row not null), and a reused mask over
+// the given grid of query tiles and heads.
 hipError_t launch_fa_fwd_gather(int rule, int unit_rows, const FwdParams& p, int bh,
                                 hipStream_t stream);
+hipError_t launch_fa_fwd_mask(int unit_rows, const FwdParams& p, dim3 grid, hipStream_t stream);
 
 // Enqueue a fill of n uint64 zeros (a kernel rather than a memset node, so the call can be
 // captured into a graph and replayed).

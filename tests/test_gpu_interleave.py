@@ -9,13 +9,13 @@ pytestmark = pytest.mark.gpu
 # (heads, tokens): groups of 8, 4, 2 and 1 with ragged last tiles; one query tile a head;
 # a leftover single head; tile counts that the group size does not divide.
 SHAPES = [(15, 36 * 128 - 5), (43, 13 * 128 - 100), (130, 4 * 128), (520, 100), (2, 257 * 128 + 1)]
-# A reused mask's launch leaves an odd head count in grid order up to 320 query tiles: groups of
-# 8, 4 and 2, and leftover single heads above that.
+# Groups of 8, 4 and 2 and leftover single heads above 320 query tiles, where a reused mask's
+# launch interleaves whatever it reports.
 MASK_SHAPES = SHAPES + [(14, 37 * 128 - 5), (3, 321 * 128 - 70), (5, 320 * 128 + 1)]
-# An MX-FP8 launch interleaves if its last round of 512 workgroups is at least 0.8 full: the
-# same groups at such counts (the least full of them 410, one below 409).
-MXFP8_SHAPES = SHAPES + [(15, 64 * 128 - 5), (43, 23 * 128 - 100), (130, 7 * 128), (922, 100),
-                         (921, 100), (5, 193 * 128 + 1), (4, 256 * 128)]
+# MX-FP8 rules interleave up to 64 query tiles, and up to 256 if the last round of 512 workgroups
+# is at least 0.8 full: the same groups on both sides of these lines.
+MXFP8_SHAPES = SHAPES + [(15, 64 * 128 - 5), (15, 65 * 128 - 5), (11, 64 * 128 + 1),
+                         (8, 115 * 128 - 9), (5, 193 * 128 + 1), (4, 256 * 128), (2, 300 * 128)]
 
 
 @pytest.fixture(scope="module", autouse=True)
