@@ -23,7 +23,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kChunks = 4;               // 8-value chunks per thread
@@ -78,19 +78,14 @@ __device__ __forceinline__ void quantize_chunk(const u32x4& w, const float (&sh)
     }
     amax = __float_as_uint(m);
   } else {
-    u16x2 m = __builtin_bit_cast(u16x2, w[0] & 0x7fff7fffu);
+    // Plus 0x7f, magnitudes up to infinity's 0x7f80 stay positive 16-bit integers and a NaN's
+    // turn negative, below zero's.
+    i16x2 m{0x7f, 0x7f};
 #pragma unroll
-    for (int j = 1; j < 4; ++j)
-      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
-    amax = (uint32_t)max(m[0], m[1]) << 16;
-    if (amax > 0x7f800000u) {          // rare: a NaN among them
-      amax = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t lo = w[j] << 16 & 0x7fff0000u, hi = w[j] & 0x7fff0000u;
-        amax = max(amax, max(lo <= 0x7f800000u ? lo : 0u, hi <= 0x7f800000u ? hi : 0u));
-      }
-    }
+    for (int j = 0; j < 4; ++j)
+      m = __builtin_elementwise_max(
+          m, __builtin_bit_cast(i16x2, (w[j] & 0x7fff7fffu) + 0x007f007fu));
+    amax = (uint32_t)(max(m[0], m[1]) - 0x7f) << 16;
   }
   amax = quad_max(amax);
   // floor(log2 amax) - 8 + 127 is the biased exponent minus 8; zero and tiny blocks (and
