@@ -440,7 +440,8 @@ def dsattn_quantize_mxfp8(x, codes=None, scales=None, shift=None, stream=None):
 
 def dsattn_key_mean(k, out=None, stream=None):
     """Mean key of every head: float32 [B, H, d] of a contiguous bf16 GPU tensor
-    [B, H, N, d] (fixed summation order)."""
+    [B, H, N, d] (fixed summation order).  With many keys the call takes scratch from the pool
+    of its stream, except under capture or where memory is short (same bits)."""
     import torch
 
     if k.dtype != torch.bfloat16 or not k.is_cuda or not k.is_contiguous() or k.dim() != 4:
